@@ -71,9 +71,10 @@ enum {
  *        (rows 32b .. 32b+15 = gate rows 16b .. 16b+15, rows 32b+16 .. 32b+31 =
  *        up rows 16b .. 16b+15); silu(z) = z / (1 + e^-z).
  *   workspace: ssa_linear_workspace_size bytes (0 when one pass over K fills the
- *        chip).  Its first words are split tickets: zero before the first call
- *        (a zeroed allocation), and zero again after every call.  Calls that
- *        share a workspace must be ordered on one stream.
+ *        chip).  Its first 256 bytes are split tickets, whatever the sizes: zero
+ *        before the first call (a zeroed allocation), and zero again after every
+ *        call.  Calls that share a workspace, of one size or several, must be
+ *        ordered on one stream.
  * Requires N % 128 == 0 and K % 64 == 0; M >= 0 (M == 0 does nothing); M K and N K
  * below 2^40 and (M / 32 + 1) (N / 128) at most 2^24.
  * Results do not depend on the launch order of workgroups: split partials are

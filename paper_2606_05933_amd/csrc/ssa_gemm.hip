@@ -6,24 +6,40 @@
 // torch Linear layout), fp32 accumulation.
 //  * One workgroup per output tile and K range.  A tile configuration
 //    (TileCfg) sets the wave grid and each wave's share in
-//    v_mfma_f32_16x16x32_bf16 tiles: 128 x 128 on 2 x 2 waves of 64 x 64,
-//    256 x 256 on 2 x 4 waves of 128 x 64, 64 x 128 on 2 x 2 waves of 32 x 64,
-//    32 x 256 on 1 x 4 waves of 32 x 64.  The host picks one per shape.
+//    v_mfma_f32_16x16x32_bf16 tiles; the host picks one per shape.
 //  * W is the MFMA A operand (MFMA rows = output columns n) and x the B operand
 //    (MFMA columns = tokens), so a lane ends with 4 consecutive n of one token:
 //    one 8-byte store per 16 x 16 tile.
 //  * K blocks of 64 are copied global -> LDS without registers
-//    (global_load_lds_dwordx4) into a ring of STAGES stages, STAGES - 1 blocks
-//    ahead; one barrier per block.  LDS rows are 128 bytes; the 16-byte chunk c
-//    of row r sits at chunk c ^ (r & 7), so the 16 rows one ds_read_b128 reads
-//    fall on 8 distinct chunk slots per lane octet (no bank conflict).
-//  * Rows of x past M are read from row M - 1 (in bounds) and never stored.
+//    (global_load_lds_dwordx4, a scalar row base and one 32-bit lane offset)
+//    into a ring of STAGES stages; one barrier per block.  LDS rows are 128
+//    bytes; the 16-byte chunk c of row r sits at chunk c ^ (r & 7), so the 16
+//    rows one ds_read_b128 reads fall on 8 distinct chunk slots per lane octet
+//    (no bank conflict).
+//  * The loop is software-pipelined over the two K halves of a block: while the
+//    MFMAs of one half run, the fragments of the next half are read, across the
+//    barrier too (it sits between a block's halves, where the next block has
+//    landed and this block's reads are done, so its stage is refilled at once),
+//    and the copies go out one by one between the rows of MFMAs.  Reading a
+//    block's fragments only after its barrier left the matrix cores idle for
+//    the LDS reads of every block (4096 x 4096 x 14336: 410 us, now 337 us).
+//  * Rows of x past M are read from the 8-row piece of row M - 1 (in bounds) and
+//    never stored.
+//  * With one M tile, W is read once by the whole chip: its copies carry the
+//    non-temporal hint, and tile t starts its K loop at block 3 t so that
+//    neighbouring tiles, whose rows are a power of two apart, do not all walk
+//    the same memory channels (24 x 28672 x 4096: 58 -> 36 us, 6.5 TB/s; 128
+//    rows: 66 -> 47 us).  With several M tiles neither: they share W and x
+//    panels through the caches, which wants them on the same K block.
 //  * Too few tiles to fill the chip: K is split; each split writes its fp32
 //    tile with device-scope stores, takes a ticket, and the last one adds the
 //    splits in split order (the result does not depend on arrival order),
-//    applies the epilogue and resets the ticket.
-//  * Work ids are laid out so that consecutive ids (the M tiles of one N tile,
-//    which read the same W panel) run on one XCD and share its L2.
+//    applies the epilogue and resets the ticket.  Merging neighbours pairwise up
+//    a tree instead (each workgroup reads at most log2(splits) tiles) measured
+//    slower: a level costs a store, a ticket and a read one after the other
+//    (24 x 4096 x 14336 in 4 splits: 35 against 23.5 us).
+//  * Work ids are laid out so that consecutive ids run on one XCD and share its
+//    L2: groups of M tiles by N tiles.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -39,6 +55,8 @@ constexpr int kNormThreads = 256;
 constexpr int BK = 64;  // K block: one 128-byte LDS row per operand row
 constexpr int kXcds = 8;
 constexpr float kLog2e = 1.4426950408889634f;
+// From here on 7 rows of 2 K bytes and a chunk pass 32 bits: 64-bit addresses.
+constexpr int kWideK = 1 << 28;
 
 // Split partials cross workgroups and XCDs (whose L2s are not coherent with
 // each other): device-scope 8-byte stores, device-coherent loads (below), a
@@ -78,10 +96,10 @@ struct GemmArgs {
   const uint16_t* w;
   const uint16_t* res;
   uint16_t* out;
-  int* tickets;
+  uint32_t* tickets;
   float* part;
   int m, n, k;
-  int tiles_m, tiles_n, splits, kbps, kblocks;
+  int tiles_m, tiles_n, splits, kbps, kblocks, group;
 };
 
 // A tile configuration: NWM x NWN waves, each owning TM x TN MFMA tiles of
@@ -96,68 +114,102 @@ struct TileCfg {
   static constexpr int kPieces = (BM + BN) / 8;      // 1 KB copies (8 rows) per stage
   static constexpr int kLoads = kPieces / kWaves;    // copies per wave per stage
   static constexpr int kTileFloats = BM * BN;
+  static constexpr bool kRoll = TM >= 4;             // x fragments replaced row by row
   static_assert(kPieces % kWaves == 0, "copies must split evenly over the waves");
   static_assert(TN % 2 == 0, "the SwiGLU epilogue pairs n tiles");
-  static_assert((STAGES - 2) * kLoads < 64, "vmcnt range");
+  static_assert(OCC * STAGES * kStage <= 160 * 1024, "LDS of a CU");
+  static_assert((STAGES - 1) * kLoads < 64, "vmcnt range");
 };
 
-// Wait until at most `left` K blocks (LOADS copies each) of this wave are in flight.
-template <int STAGES, int LOADS>
+// Wait until at most min(left, MAX) K blocks (LOADS copies each) of this wave
+// are in flight.
+template <int MAX, int LOADS>
 __device__ __forceinline__ void wait_blocks(int left) {
-  if (STAGES >= 4 && left >= 2) vm_wait<2 * LOADS>();
-  else if (STAGES >= 3 && left >= 1) vm_wait<LOADS>();
-  else vm_wait<0>();
+  if constexpr (MAX <= 0) {
+    vm_wait<0>();
+  } else {
+    if (left >= MAX) vm_wait<MAX * LOADS>();
+    else wait_blocks<MAX - 1, LOADS>(left);
+  }
 }
 
-template <class C, int EPI>
+// Barrier of a K block: this wave's LDS reads have returned, and no memory
+// access moves across (copies in flight stay in flight).
+__device__ __forceinline__ void block_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// MODE: kShared, several M tiles; kStream, one M tile (W copies with the
+// non-temporal hint, staggered K loops); kWide, rows too long for a 32-bit lane
+// offset (7 rows of 2 K bytes): 64-bit lane addresses.
+enum { kShared, kStream, kWide };
+template <class C, int EPI, int MODE>
 __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a) {
   constexpr int TM = C::TM, TN = C::TN, STAGES = C::STAGES, LOADS = C::kLoads;
   constexpr int BM = C::BM, BN = C::BN;
   __shared__ __attribute__((aligned(16))) char lds[STAGES * C::kStage];
-  // The split reduction's "last arriver" flag shares the ring's first word: it
-  // is written after every wave has drained its copies (vmcnt(0)) and passed a
-  // barrier behind its last ring read.  (A separate word would take the
-  // 192-row tile's two workgroups 8 bytes past the CU's 160 KB.)
-  int& s_last = *reinterpret_cast<int*>(lds);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w / C::NWN, wn = w % C::NWN;
   const int r16 = lane & 15, g = lane >> 4;
 
-  // work id: consecutive ids on one XCD (dispatch goes round-robin over XCDs)
+  // work id: consecutive ids on one XCD (dispatch goes round-robin over XCDs);
+  // tiles in groups of `group` M tiles by all N tiles, splits outermost
   const int total = (int)gridDim.x, xcd = (int)blockIdx.x % kXcds, local = (int)blockIdx.x / kXcds;
   const int per = total / kXcds, rem = total % kXcds;
   const int wid = xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
-  const int tm = wid % a.tiles_m;
-  const int tn = (wid / a.tiles_m) % a.tiles_n;
-  const int split = wid / (a.tiles_m * a.tiles_n);
+  const int tiles = a.tiles_m * a.tiles_n, tile = wid % tiles, split = wid / tiles;
+  const int gi = tile / (a.group * a.tiles_n), gr = min(a.group, a.tiles_m - gi * a.group);
+  const int gl = tile - gi * a.group * a.tiles_n;
+  const int tm = gi * a.group + gl % gr, tn = gl / gr;
   const int m0 = tm * BM, n0 = tn * BN;
   const int kb0 = split * a.kbps;
   const int nkb = min(a.kbps, a.kblocks - kb0);
+  const int rot = MODE == kStream ? (tile * 3) % nkb : 0;  // the K block this tile starts with
 
   // Copy r of this wave fills 1 KB piece p = kWaves r + w of a stage: pieces
   // below BM / 8 hold x rows 8p..8p+7, the rest W rows; lane i fetches the
-  // chunk that belongs at its LDS slot (row 8p + i / 8, slot i % 8).
-  const uint16_t* src[LOADS];
+  // chunk that belongs at its LDS slot (row 8p + i / 8, slot i % 8).  The piece
+  // of x row M - 1 repeats that row past M, and pieces past M read that piece.
+  const uint32_t lrow = lane >> 3, chunk = ((lane & 7) ^ (lane >> 3)) * 16;
+  const uint32_t lrow_end = min(lrow, (uint32_t)(a.m - 1) & 7);
+  const char* src[LOADS];
+  uint32_t off[LOADS];
 #pragma unroll
   for (int r = 0; r < LOADS; ++r) {
     const int p = r * C::kWaves + w;
-    const int chunk = (lane & 7) ^ (lane >> 3);
-    if (p < BM / 8) {
-      const int row = p * 8 + (lane >> 3);
-      src[r] = a.x + (size_t)min(m0 + row, a.m - 1) * a.k + (size_t)kb0 * BK + chunk * 8;
+    const bool isx = p < BM / 8;
+    const int row0 = isx ? m0 + p * 8 : n0 + p * 8 - BM;
+    const bool full = !isx || row0 + 8 <= a.m;
+    const int row = full ? row0 : (a.m - 1) & ~7;
+    src[r] = reinterpret_cast<const char*>(isx ? a.x : a.w) + ((size_t)row * a.k + (size_t)kb0 * BK) * 2;
+    if (MODE == kWide) {
+      src[r] += (size_t)(full ? lrow : lrow_end) * a.k * 2 + chunk;
+      off[r] = 0;
     } else {
-      const int row = (p - BM / 8) * 8 + (lane >> 3);
-      src[r] = a.w + (size_t)(n0 + row) * a.k + (size_t)kb0 * BK + chunk * 8;
+      off[r] = (full ? lrow : lrow_end) * (uint32_t)a.k * 2 + chunk;
     }
   }
-  auto issue = [&](int i) {
-    const char* st = lds + (i % STAGES) * C::kStage;
-#pragma unroll
-    for (int r = 0; r < LOADS; ++r)
-      dma16(src[r] + (size_t)i * BK, st + (r * C::kWaves + w) * 1024);
+  auto copy = [&](int r, size_t koff, const char* dst) {
+    const uint32_t l = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)dst;
+    if (MODE == kWide)
+      dma16(src[r] + koff, dst);
+    else if (MODE == kStream && r * C::kWaves + w >= BM / 8)
+      asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(off[r]), "s"(src[r] + koff), "{m0}"(l)
+                   : "memory");
+    else
+      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off[r]), "s"(src[r] + koff), "{m0}"(l)
+                   : "memory");
+  };
+  auto block_off = [&](int i) {  // byte offset of the tile's i-th K block along a row
+    int kb = i + rot;
+    kb = kb >= nkb ? kb - nkb : kb;
+    return (size_t)kb * (BK * 2);
   };
 
-  // fragment reads: row r16 of a 16-row tile, logical chunk 4 ks + g
+  // fragment reads: row r16 of a 16-row tile, logical chunk 4 half + g
   const int xoff = (wm * TM * 16 + r16) * 128;
   const int woff = BM * 128 + (wn * TN * 16 + r16) * 128;
   const int c0 = (g ^ (r16 & 7)) << 4, c1 = ((4 + g) ^ (r16 & 7)) << 4;
@@ -167,54 +219,102 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Fragments of the two halves.  kRoll: x rows 0 .. TM - 3 share one register
+  // set (row t of the next half is read once row t's MFMAs are issued), the
+  // last two rows have two, so their reads go out before the barrier nears.
+  bf16x8 xf[2][TM], wf[2][TN];
+  auto xr = [&](int b, int t) -> bf16x8& { return C::kRoll && t < TM - 2 ? xf[0][t] : xf[b][t]; };
+  auto read_x = [&](int b, const char* p, int t) { xr(b, t) = as_bf16x8(ld16(p + xoff + t * 2048)); };
+  auto read_w = [&](int b, const char* p, int t) { wf[b][t] = as_bf16x8(ld16(p + woff + t * 2048)); };
+
+  int st = 0;  // stage of the current block
+  // MFMAs of half b, a row of TN at a time; between the rows the fragments of
+  // the other half are read from p and, with `fill`, block i's copies go out to
+  // stage st.
+  auto half = [&](int b, const char* p, bool fill, int i) {
+    const size_t koff = fill ? block_off(i) : 0;
+    const char* dst = lds + st * C::kStage + w * 1024;
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+#pragma unroll
+      for (int nt = 0; nt < TN; ++nt) acc[t][nt] = mfma(wf[b][nt], xr(b, t), acc[t][nt]);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (C::kRoll) {
+        if (t < TM - 2) {
+          read_x(b ^ 1, p, t);
+#pragma unroll
+          for (int j = t * TN / (TM - 2); j < (t + 1) * TN / (TM - 2); ++j) read_w(b ^ 1, p, j);
+          if (t >= TM - 4) read_x(b ^ 1, p, t + 2);
+        }
+      } else {
+        constexpr int PER = (TM + TN + TM - 1) / TM;
+#pragma unroll
+        for (int j = t * PER; j < (t + 1) * PER; ++j)
+          if (j < TN) read_w(b ^ 1, p, j);
+          else if (j < TN + TM) read_x(b ^ 1, p, j - TN);
+      }
+      if (fill && t * LOADS / TM < (t + 1) * LOADS / TM) {
+#pragma unroll
+        for (int r = t * LOADS / TM; r < (t + 1) * LOADS / TM; ++r)
+          copy(r, koff, dst + r * C::kWaves * 1024);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
 
 #pragma unroll
-  for (int i = 0; i < STAGES - 1; ++i)
-    if (i < nkb) issue(i);
-  for (int i = 0; i < nkb; ++i) {
-    wait_blocks<STAGES, LOADS>(min(nkb - 1 - i, STAGES - 2));
-    __syncthreads();  // block i has landed for every wave; stage (i - 1) % STAGES is free
-    if (i + STAGES - 1 < nkb) issue(i + STAGES - 1);
-    const char* st = lds + (i % STAGES) * C::kStage;
+  for (int i = 0; i < STAGES; ++i)
+    if (i < nkb) {
+      const size_t koff = block_off(i);
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int c = ks ? c1 : c0;
-      bf16x8 xf[TM], wf[TN];
-#pragma unroll
-      for (int t = 0; t < TM; ++t) xf[t] = as_bf16x8(ld16(st + xoff + t * 2048 + c));
-#pragma unroll
-      for (int t = 0; t < TN; ++t) wf[t] = as_bf16x8(ld16(st + woff + t * 2048 + c));
-#pragma unroll
-      for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < TN; ++nt) acc[mt][nt] = mfma(wf[nt], xf[mt], acc[mt][nt]);
+      for (int r = 0; r < LOADS; ++r)
+        copy(r, koff, lds + i * C::kStage + (r * C::kWaves + w) * 1024);
     }
+  wait_blocks<STAGES - 1, LOADS>(nkb - 1);
+  block_barrier();
+#pragma unroll
+  for (int t = 0; t < TN; ++t) read_w(0, lds + c0, t);
+#pragma unroll
+  for (int t = 0; t < TM; ++t) read_x(0, lds + c0, t);
+  for (int i = 0; i < nkb; ++i) {
+    const int next = st + 1 == STAGES ? 0 : st + 1;
+    half(0, lds + st * C::kStage + c1, false, 0);
+    // block i + 1 has landed (this wave's copies, then everyone's), and every
+    // wave has read all of block i: its stage takes block i + STAGES.  Past the
+    // last block the reads return an older block's fragments, which go unused.
+    wait_blocks<STAGES - 2, LOADS>(nkb - 2 - i);
+    block_barrier();
+    half(1, lds + next * C::kStage + c0, i + STAGES < nkb, i + STAGES);
+    st = next;
   }
 
   // 16-token tiles of this wave that hold rows < M (wave-uniform)
   const int nmt = max(0, min(TM, (a.m - (m0 + wm * TM * 16) + 15) / 16));
   if (a.splits > 1) {
-    const int tile = tn * a.tiles_m + tm;
-    const size_t wbase = (size_t)w * (TM * TN * 256) + lane * 4;
-    float* mine = a.part + ((size_t)tile * a.splits + split) * C::kTileFloats + wbase;
+    int& s_last = *reinterpret_cast<int*>(lds);
+    float* const parts = a.part + (size_t)tile * a.splits * C::kTileFloats;
+    const int mine = w * (TM * TN * 256) + lane * 4;
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt)
       if (mt < nmt)
 #pragma unroll
-        for (int nt = 0; nt < TN; ++nt) st16_dev(mine + (mt * TN + nt) * 256, acc[mt][nt]);
-    vm_wait<0>();  // this thread's device-scope stores have completed
-    __syncthreads();
+        for (int nt = 0; nt < TN; ++nt)
+          st16_dev(parts + (size_t)split * C::kTileFloats + mine + (mt * TN + nt) * 256, acc[mt][nt]);
+    vm_wait<0>();     // this thread's device-scope stores have completed
+    __syncthreads();  // everyone's have, and the ring is free
+    // the tile's 4-bit counter: tile % 64 names the word, tile / 64 the nibble
+    uint32_t* const word = a.tickets + tile % 64;
+    const int shift = tile / 64 * 4;
     if (tid == 0) {
-      const int prev =
-          __hip_atomic_fetch_add(&a.tickets[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = (prev == a.splits - 1);
+      const uint32_t prev =
+          __hip_atomic_fetch_add(word, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = (int)((prev >> shift) & 15) == a.splits - 1;
     }
     __syncthreads();
     if (!s_last) return;
     // sum in split order, own split from registers (the same bits it stored);
     // the partials of four splits are in flight at once
-    const PartReader rd(a.part + (size_t)tile * a.splits * C::kTileFloats);
-    const int wb = (int)wbase * 4;
+    const PartReader rd(parts);
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt) {
       if (mt >= nmt) continue;
@@ -229,7 +329,7 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
 #pragma unroll
           for (int nt = 0; nt < TN; ++nt)
             v[j][nt] = (s < a.splits && s != split)
-                           ? rd((s * C::kTileFloats + (mt * TN + nt) * 256) * 4 + wb)
+                           ? rd((s * C::kTileFloats + mine + (mt * TN + nt) * 256) * 4)
                            : acc[mt][nt];
         }
 #pragma unroll
@@ -241,7 +341,9 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
 #pragma unroll
       for (int nt = 0; nt < TN; ++nt) acc[mt][nt] = tot[nt];
     }
-    if (tid == 0) __hip_atomic_store(&a.tickets[tile], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0)
+      __hip_atomic_fetch_sub(word, (uint32_t)a.splits << shift, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
   }
 
   // epilogue: lane holds n = nbase + 4 g .. + 3 of token m0 + wm TM 16 + 16 mt + r16
@@ -319,129 +421,135 @@ __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(const uint16_t* 
   }
 }
 
-// The tile configurations the host chooses from.
-using CfgMid2 = TileCfg<2, 2, 4, 4, 2, 2>;   // 128 x 128, 4 waves of 64 x 64, two per CU
-using CfgBig = TileCfg<2, 4, 8, 4, 2, 1>;    // 256 x 256, 8 waves of 128 x 64
-using CfgM64 = TileCfg<2, 2, 2, 4, 3, 2>;    // 64 x 128, 4 waves of 32 x 64, two per CU
-using CfgTiny = TileCfg<1, 4, 2, 4, 4, 1>;   // 32 x 256: few tokens, weight streaming
-using CfgM160 = TileCfg<2, 2, 5, 4, 2, 2>;   // 160 x 128, 4 waves of 80 x 64, two per CU
-using CfgM192 = TileCfg<2, 2, 6, 4, 2, 2>;   // 192 x 128, 4 waves of 96 x 64, two per CU
-enum { kCfgMid2, kCfgBig, kCfgM64, kCfgTiny, kCfgM160, kCfgM192, kNumCfgs };
+// The tile configurations the host chooses from, by tokens x output features.
+using Cfg32x64 = TileCfg<2, 2, 1, 2, 6, 2>;
+using Cfg64x64 = TileCfg<2, 2, 2, 2, 5, 2>;
+using Cfg64x128 = TileCfg<2, 2, 2, 4, 3, 2>;
+using Cfg96x64 = TileCfg<2, 2, 3, 2, 5, 1>;
+using Cfg96x128 = TileCfg<2, 2, 3, 4, 5, 1>;
+using Cfg128x64 = TileCfg<2, 2, 4, 2, 6, 1>;
+using Cfg128x128 = TileCfg<2, 4, 4, 2, 5, 1>;
+using Cfg160x128 = TileCfg<2, 2, 5, 4, 2, 2>;
+using Cfg192x128 = TileCfg<4, 2, 3, 4, 4, 1>;
+using Cfg192x128x2 = TileCfg<2, 2, 6, 4, 2, 2>;
+using Cfg256x128 = TileCfg<4, 2, 4, 4, 3, 1>;
+using Cfg256x256 = TileCfg<2, 4, 8, 4, 2, 1>;
+enum {
+  kCfg32x64, kCfg64x64, kCfg64x128, kCfg96x64, kCfg96x128, kCfg128x64, kCfg128x128,
+  kCfg160x128, kCfg192x128, kCfg192x128x2, kCfg256x128, kCfg256x256, kNumCfgs
+};
 
 struct CfgShape {
-  int bm, bn, occ;
+  int bm, bn, occ, stages;
 };
 template <class C>
 constexpr CfgShape shape_of() {
-  return CfgShape{C::BM, C::BN, C::OCC};
+  return CfgShape{C::BM, C::BN, C::OCC, C::STAGES};
 }
-constexpr CfgShape kCfgShapes[kNumCfgs] = {shape_of<CfgMid2>(), shape_of<CfgBig>(),
-                                           shape_of<CfgM64>(),  shape_of<CfgTiny>(),
-                                           shape_of<CfgM160>(), shape_of<CfgM192>()};
+constexpr CfgShape kCfgShapes[kNumCfgs] = {
+    shape_of<Cfg32x64>(),   shape_of<Cfg64x64>(),   shape_of<Cfg64x128>(),    shape_of<Cfg96x64>(),
+    shape_of<Cfg96x128>(),  shape_of<Cfg128x64>(),  shape_of<Cfg128x128>(),   shape_of<Cfg160x128>(),
+    shape_of<Cfg192x128>(), shape_of<Cfg192x128x2>(), shape_of<Cfg256x128>(), shape_of<Cfg256x256>()};
 
 struct GemmPlan {
   int cfg, tiles_m, tiles_n, splits, kbps, kblocks;
-  size_t tickets, ws;
+  size_t ws;
 };
 
 constexpr int kCus = 256;
+// Split tickets: a 4-bit counter per tile in the workspace's first 256 bytes,
+// whatever the shape, so that products of different shapes can share a
+// workspace (the partials of one never lie where another's tickets are).
+constexpr size_t kTicketBytes = 256;
+constexpr int kMaxSplitTiles = (int)kTicketBytes * 2, kMaxSplits = 15;
 
-// Split K when the tiles alone leave the chip under target_wgs workgroups
-// (at least 4 K blocks per split).  Tiles that overfill the chip by a partial
-// round are not split: measured on MI355X, the extra partials cost about what
-// the evened rounds save (an even spread needs per-unit scheduling instead).
-GemmPlan gemm_plan(int cfg, int m, int n, int k, int target_wgs) {
+// cfg's tiles in (up to) s K splits; one where the tickets do not suffice.
+GemmPlan make_plan(int cfg, int m, int n, int k, int s) {
   const CfgShape& cs = kCfgShapes[cfg];
   GemmPlan c;
   c.cfg = cfg;
   c.tiles_m = (m + cs.bm - 1) / cs.bm;
   c.tiles_n = n / cs.bn;
   c.kblocks = k / BK;
-  const int tiles = c.tiles_m * c.tiles_n;
-  int s = 1;
-  if (tiles < target_wgs / 2) s = (target_wgs + tiles - 1) / tiles;
-  s = std::max(1, std::min(s, c.kblocks / 4));
+  s = std::max(1, std::min({s, c.kblocks, kMaxSplits}));
+  if ((int64_t)c.tiles_m * c.tiles_n > kMaxSplitTiles) s = 1;
   c.kbps = (c.kblocks + s - 1) / s;
   c.splits = (c.kblocks + c.kbps - 1) / c.kbps;
-  c.tickets = ((size_t)tiles * 4 + 255) / 256 * 256;
-  c.ws = c.splits > 1 ? c.tickets + (size_t)tiles * c.splits * cs.bm * cs.bn * 4 : 0;
+  c.ws = c.splits > 1 ? kTicketBytes + (size_t)c.tiles_m * c.tiles_n * c.splits * cs.bm * cs.bn * 4 : 0;
   return c;
 }
 
-// The same tiles in (up to) s K splits of at least 4 K blocks.
-GemmPlan split_plan(GemmPlan c, int s) {
+// Microseconds a workgroup of each configuration takes per K block of 64, with
+// one and (OCC 2) two of them on every CU.  Fitted, with the constants of
+// plan_cost, to 290 products timed on MI355X in every configuration and 1 to 12
+// splits, weights out of the caches (M = 1 .. 4096; N x K of the Llama-3-8B
+// projections and 640 x 640 .. 16384 x 8192): the plan picked is 1.2% slower than
+// the fastest measured on the mean (14% at worst) and takes 0.68 of hipBLASLt's
+// time on the geometric mean (0.94 at M = 2176, 1.1 at M = 4096).
+constexpr double kBlockUs[kNumCfgs][2] = {
+    {0.182, 0.293}, {0.239, 0.475}, {0.380, 0.629}, {0.281, 0.281}, {0.453, 0.453}, {0.379, 0.379},
+    {0.521, 0.521}, {0.832, 1.126}, {0.662, 0.662}, {0.924, 1.278}, {0.827, 0.827}, {1.447, 1.447}};
+
+// Estimated microseconds of a plan: rounds of the chip's workgroup slots times
+// a workgroup's K blocks (its pipeline's fill counted as 1.3 more; a last round
+// of the tall tiles that come two to a CU costs by the CUs that hold two), or
+// the weights' bytes (at less where the workgroups' copies in flight are too few
+// to hide the latency), whichever is larger; and for a split the last arriver's
+// reads of the other partial tiles and all their bytes.
+double plan_cost(const GemmPlan& c, int m, int n, int k) {
   const CfgShape& cs = kCfgShapes[c.cfg];
-  s = std::max(1, std::min(s, c.kblocks / 4));
-  c.kbps = (c.kblocks + s - 1) / s;
-  c.splits = (c.kblocks + c.kbps - 1) / c.kbps;
-  const size_t tiles = (size_t)c.tiles_m * c.tiles_n;
-  c.ws = c.splits > 1 ? c.tickets + tiles * c.splits * cs.bm * cs.bn * 4 : 0;
-  return c;
+  const double one = kBlockUs[c.cfg][0], two = kBlockUs[c.cfg][1];
+  const int64_t wgs = (int64_t)c.tiles_m * c.tiles_n * c.splits, slots = (int64_t)kCus * cs.occ;
+  const int64_t rest = wgs % slots;
+  double t = (double)(wgs / slots) * two;
+  if (rest > kCus) t += cs.bm >= 160 ? one + (two - one) * (double)(rest - kCus) / kCus : two;
+  else if (rest > 0) t += one;
+  t *= c.kbps + 1.3;
+  const double in_flight = (double)wgs * cs.bn * (cs.stages - 1) / 64.;
+  t = std::max(t, (double)n * k * 2. / 8.59e6 / std::min(1., in_flight / 1016.));
+  if (c.splits > 1) {
+    const double tile = (double)std::min(cs.bm, (m + 15) / 16 * 16) * cs.bn;
+    t += 3.41 + (c.splits - 1) * tile * (1.545 / 16384.);
+    t += (double)c.tiles_m * c.tiles_n * (c.splits - 1) * tile * 4. / 2.325e6;
+  }
+  return t;
 }
 
-// Among the 128 x 128, 160 x 128 and 192 x 128 tiles (two workgroups per CU)
-// and 1 or s K splits: the one whose workgroups take the fewest rounds of the
-// chip's 512 slots, counted in rows of tile per split (a last partial round
-// costs about a whole one); splits pay their partials' write and read, about
-// 1.35x on this count (measured on the down projection).  Ties go to the
-// smaller tile.
-GemmPlan fewest_rounds(int m, int n, int k, int max_splits) {
+// The cheapest plan by plan_cost over the configurations and 1 .. 12 splits of
+// at least 3 K blocks that leave at most 1100 workgroups.
+GemmPlan choose_plan(int m, int n, int k) {
+  if (k >= kWideK) return make_plan(kCfg32x64, m, n, k, 1);
   GemmPlan best{};
-  double best_cost = 1e30;
-  for (int cfg : {kCfgMid2, kCfgM160, kCfgM192}) {
-    for (int s : {1, max_splits}) {
-      const GemmPlan c = split_plan(gemm_plan(cfg, m, n, k, 1), s);
-      const CfgShape& cs = kCfgShapes[cfg];
-      const int64_t wgs = (int64_t)c.tiles_m * c.tiles_n * c.splits;
-      const int64_t slots = (int64_t)kCus * cs.occ;
-      double cost = (double)((wgs + slots - 1) / slots) * cs.bm / c.splits;
-      if (c.splits > 1) cost *= 1.35;
-      if (cost < best_cost - 1e-9) best_cost = cost, best = c;
+  double best_cost = 1e300;
+  for (int cfg = 0; cfg < kNumCfgs; ++cfg) {
+    const CfgShape& cs = kCfgShapes[cfg];
+    // half-empty tiles, and tiles far smaller than a long batch, never win
+    if (n % cs.bn || (cs.bm > 32 && cs.bm >= 2 * m) || (cs.bm < 96 && m >= 1024)) continue;
+    for (int s : {1, 2, 3, 4, 5, 6, 8, 12}) {
+      const GemmPlan c = make_plan(cfg, m, n, k, s);
+      if (s > 1 && ((int64_t)c.tiles_m * c.tiles_n * s > 1100 || c.kblocks / s < 3)) break;
+      const double cost = plan_cost(c, m, n, k);
+      if (cost < best_cost) best_cost = cost, best = c;
     }
   }
   return best;
 }
 
-// Measured on MI355X against the Llama-3-8B projections (N x K = 6144 x 4096,
-// 4096 x 4096, 28672 x 4096, 4096 x 14336) for M = 28 .. 4096, with the
-// weights out of the caches as they are inside a layer (T128 = the number of
-// 128 x 128 tiles):
-//  * M <= 64: weight streaming; 32 x 256 tiles, K split to about 128 (long K
-//    and M > 32: 256) workgroups;
-//  * M >= 1536 with at least 192 tiles of 256 x 256: those;
-//  * under-filled shapes, T128 < 256 (K > 8192: T128 < 96): 64 x 128 tiles, K-split
-//    to about 256 workgroups when there are at most 128 of them, and at least
-//    in two for K > 8192 (at M = 640: 40 against 60 us for the O projection);
-//  * otherwise fewest_rounds over 128-, 160- and 192-row tiles (1 or 3 K splits
-//    for K > 8192): gate/up at M = 384 102 against 133 us (192 rows), at
-//    M = 640 169 against 194 us (160 rows); the down projection at M = 2176
-//    252 against 342 us (160 rows unsplit).
-GemmPlan choose_plan(int m, int n, int k) {
-  const int64_t t128 = (int64_t)((m + 127) / 128) * (n / 128);
-  if (n % 256 == 0) {
-    if (m <= 64) return gemm_plan(kCfgTiny, m, n, k, (m > 32 && k > 8192) ? 256 : 128);
-    if (m >= 1536 && (int64_t)((m + 255) / 256) * (n / 256) >= 192)
-      return gemm_plan(kCfgBig, m, n, k, 256);
-  }
-  auto m64 = [&](int min_splits) {
-    const GemmPlan c = gemm_plan(kCfgM64, m, n, k, 1);
-    const int tiles = c.tiles_m * c.tiles_n;
-    return split_plan(c, std::max(min_splits, tiles <= 128 ? (256 + tiles - 1) / tiles : 1));
-  };
-  if (k > 8192) return t128 < 96 ? m64(2) : fewest_rounds(m, n, k, 3);
-  if (t128 < 256) return m64(1);
-  return fewest_rounds(m, n, k, 1);
+template <class C, int MODE>
+void launch_mode(const GemmPlan& c, int epilogue, const GemmArgs& a, hipStream_t s) {
+  const dim3 grid(c.tiles_m * c.tiles_n * c.splits), block(C::kThreads);
+  if (epilogue == SSA_EPILOGUE_NONE)
+    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_NONE, MODE>), grid, block, 0, s, a);
+  else if (epilogue == SSA_EPILOGUE_RESIDUAL)
+    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_RESIDUAL, MODE>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_SWIGLU, MODE>), grid, block, 0, s, a);
 }
 
 template <class C>
 void launch_cfg(const GemmPlan& c, int epilogue, const GemmArgs& a, hipStream_t s) {
-  const dim3 grid(c.tiles_m * c.tiles_n * c.splits), block(C::kThreads);
-  if (epilogue == SSA_EPILOGUE_NONE)
-    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_NONE>), grid, block, 0, s, a);
-  else if (epilogue == SSA_EPILOGUE_RESIDUAL)
-    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_RESIDUAL>), grid, block, 0, s, a);
-  else
-    hipLaunchKernelGGL((linear_kernel<C, SSA_EPILOGUE_SWIGLU>), grid, block, 0, s, a);
+  if (c.tiles_m == 1) launch_mode<C, kStream>(c, epilogue, a, s);
+  else launch_mode<C, kShared>(c, epilogue, a, s);
 }
 
 // Launch a planned product; the workspace has been checked against c.ws.
@@ -449,17 +557,28 @@ int launch_linear(const GemmPlan& c, int m, int n, int k, int epilogue, const ui
                   const uint16_t* w, const uint16_t* residual, uint16_t* out, void* workspace,
                   hipStream_t s) {
   GemmArgs a{x, w, residual, out,
-             static_cast<int*>(workspace),
-             c.ws > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + c.tickets) : nullptr,
-             m, n, k, c.tiles_m, c.tiles_n, c.splits, c.kbps, c.kblocks};
+             static_cast<uint32_t*>(workspace),
+             c.ws > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + kTicketBytes) : nullptr,
+             m, n, k, c.tiles_m, c.tiles_n, c.splits, c.kbps, c.kblocks,
+             // up to 8 M tiles: all of them beside each N tile; more: groups of 4
+             c.tiles_m <= 8 ? c.tiles_m : 4};
   (void)hipGetLastError();
   switch (c.cfg) {
-    case kCfgMid2: launch_cfg<CfgMid2>(c, epilogue, a, s); break;
-    case kCfgBig: launch_cfg<CfgBig>(c, epilogue, a, s); break;
-    case kCfgM64: launch_cfg<CfgM64>(c, epilogue, a, s); break;
-    case kCfgM160: launch_cfg<CfgM160>(c, epilogue, a, s); break;
-    case kCfgM192: launch_cfg<CfgM192>(c, epilogue, a, s); break;
-    default: launch_cfg<CfgTiny>(c, epilogue, a, s); break;
+    case kCfg32x64:
+      if (k >= kWideK) launch_mode<Cfg32x64, kWide>(c, epilogue, a, s);
+      else launch_cfg<Cfg32x64>(c, epilogue, a, s);
+      break;
+    case kCfg64x64: launch_cfg<Cfg64x64>(c, epilogue, a, s); break;
+    case kCfg64x128: launch_cfg<Cfg64x128>(c, epilogue, a, s); break;
+    case kCfg96x64: launch_cfg<Cfg96x64>(c, epilogue, a, s); break;
+    case kCfg96x128: launch_cfg<Cfg96x128>(c, epilogue, a, s); break;
+    case kCfg128x64: launch_cfg<Cfg128x64>(c, epilogue, a, s); break;
+    case kCfg128x128: launch_cfg<Cfg128x128>(c, epilogue, a, s); break;
+    case kCfg160x128: launch_cfg<Cfg160x128>(c, epilogue, a, s); break;
+    case kCfg192x128: launch_cfg<Cfg192x128>(c, epilogue, a, s); break;
+    case kCfg192x128x2: launch_cfg<Cfg192x128x2>(c, epilogue, a, s); break;
+    case kCfg256x128: launch_cfg<Cfg256x128>(c, epilogue, a, s); break;
+    default: launch_cfg<Cfg256x256>(c, epilogue, a, s); break;
   }
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }

@@ -130,6 +130,70 @@ def test_linear_matches_the_oracle(torch_dev, case):
     assert np.all(err <= tol)
 
 
+# Every tile configuration with one and several M tiles, unsplit and K-split, at
+# ragged M (the last rows of a tile, of a 16-row tile and of an 8-row copy piece
+# cut), one K block (fewer than the ring's stages), and K blocks that do not
+# divide by the splits.
+TILE_EDGES = [
+    (1, 128, 64, NONE), (1, 128, 2112, RES), (33, 128, 64, SWIGLU), (33, 128, 2112, NONE),   # 32 x 64
+    (7, 384, 640, SWIGLU), (9, 384, 3200, NONE), (31, 1280, 448, RES),
+    (65, 5504, 64, RES), (97, 1536, 4096, NONE), (33, 2816, 4096, SWIGLU),                    # 64 x 64
+    (258, 5504, 64, NONE), (33, 28672, 192, SWIGLU),                                          # 64 x 128
+    (1033, 128, 64, RES), (1038, 128, 2112, NONE), (65, 2816, 4096, SWIGLU),                  # 96 x 64
+    (260, 6784, 64, SWIGLU), (91, 28672, 320, NONE),                                          # 96 x 128
+    (193, 5504, 64, NONE), (97, 4224, 4096, RES),                                             # 128 x 64
+    (386, 6656, 64, SWIGLU), (105, 28672, 192, RES),                                          # 128 x 128
+    (1030, 6656, 64, RES), (1030, 6656, 576, SWIGLU),                                         # 160 x 128
+    (515, 7296, 64, NONE), (515, 7296, 320, SWIGLU),                                          # 192 x 128
+    (1137, 6784, 64, NONE), (1137, 6784, 192, RES),                                           # 192 x 128, two per CU
+    (775, 6656, 64, SWIGLU), (775, 6656, 448, NONE),                                          # 256 x 128
+    (1539, 7424, 64, NONE), (1539, 7424, 128, RES), (1539, 7424, 576, SWIGLU),                # 256 x 256
+]
+
+
+@pytest.mark.parametrize("case", range(len(TILE_EDGES)))
+def test_linear_tile_edges_match_the_oracle(torch_dev, case):
+    from dense_ref import to_f32
+    m, n, k, epi = TILE_EDGES[case]
+    say(f"[gpu linear edges] M={m} N={n} K={k} epilogue={epi}")
+    x, w_ref, w_dev, res = inputs(m, n, k, epi, seed=500 + case)
+    got, ws_bytes = run(torch_dev, m, n, k, epi, x, w_dev, res)
+    rows = np.unique(np.r_[0, np.arange(max(0, m - 40), m), np.arange(0, m, 61)])
+    ref, tol = reference(x, w_ref, res, epi, rows)
+    err = np.abs(to_f32(got[rows]).astype(np.float64) - ref)
+    say(f"    ws={ws_bytes} max_err={err.max():.3e} worst_ratio={(err / tol).max():.3f}")
+    assert np.all(err <= tol)
+    assert np.isfinite(to_f32(got)).all()
+
+
+def test_linear_products_of_different_shapes_share_a_workspace(torch_dev):
+    """Calls ordered on one stream may share a workspace whatever their shapes: a
+    product's partial tiles must not lie where another's tickets are.  Each round
+    has new activations, so a tile that is not written again shows."""
+    from paper_2606_05933_amd import ssa, workload
+    torch = torch_dev
+    shapes = [(128, 6144, 4096), (128, 4096, 4096), (128, 4096, 14336), (24, 6144, 4096),
+              (65, 2816, 4096), (500, 2048, 8192)]
+    ws = torch.zeros(max(ssa.linear_workspace_size(*s) for s in shapes), dtype=torch.uint8,
+                     device="cuda")
+    weights = [dev_bf16(torch, workload.normal_bf16((n, k), i, k ** -0.5))
+               for i, (_, n, k) in enumerate(shapes)]
+    outs = [torch.empty((m, n), dtype=torch.bfloat16, device="cuda") for m, n, _ in shapes]
+    for r in range(3):
+        xs = [dev_bf16(torch, workload.normal_bf16((m, k), 50 * r + i + 10))
+              for i, (m, _, k) in enumerate(shapes)]
+        for x, w, out in zip(xs, weights, outs):
+            ssa.linear(x, w, out, workspace=ws)
+        for (m, n, k), x, w, out in zip(shapes, xs, weights, outs):
+            say(f"[gpu linear shared workspace] round {r} M={m} N={n} K={k}")
+            own = torch.zeros(max(ssa.linear_workspace_size(m, n, k), 4), dtype=torch.uint8,
+                              device="cuda")
+            alone = torch.empty_like(out)
+            ssa.linear(x, w, alone, workspace=own)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), alone.view(torch.int16))
+
+
 def test_linear_residual_in_place(torch_dev):
     from dense_ref import to_f32
     m, n, k = 200, 512, 1024
