@@ -448,19 +448,100 @@ __device__ void merge_pass(const AttnArgs& a, const WorkItem& it, const ReqEntry
   }
 }
 
+// The same for at most kLdsMergeSplits splits, the maxima and sums once per column
+// and not in every pass: one thread per column reads every split's m and l at
+// once and leaves the splits' weights and the column's 1 / l in LDS; then the o
+// quads are read, U units of F splits in flight.
+constexpr int kLdsMergeSplits = 16;
+template <int D, int U, int F>
+__device__ void merge_lds(const AttnArgs& a, const WorkItem& it, const ReqEntry& rq,
+                          const RecordReader& rd, int C, int S, char* lds) {
+  constexpr int UPC = D / 4;  // units (column, four dims) per column
+  const int units = C * UPC, tid = threadIdx.x;
+  const int rec = (int)rec_floats(C, D), o_off = (int)rec_o_off(C);
+  float* const wt = reinterpret_cast<float*>(lds);  // [S][C], then 1 / l [C]
+  float* const inv = wt + S * C;
+  if (tid < C) {
+    float m[kLdsMergeSplits], l[kLdsMergeSplits];
+#pragma unroll
+    for (int s = 0; s < kLdsMergeSplits; ++s) {
+      m[s] = s < S ? rd(s * rec + tid) : kNegInf;
+      l[s] = s < S ? rd(s * rec + C + tid) : 0.f;
+    }
+    float M = kNegInf, L = 0.f;
+#pragma unroll
+    for (int s = 0; s < kLdsMergeSplits; ++s) M = fmaxf(M, m[s]);
+#pragma unroll
+    for (int s = 0; s < kLdsMergeSplits; ++s) {
+      const float w = m[s] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m[s] - M);
+      L += w * l[s];
+      if (s < S) wt[s * C + tid] = w;
+    }
+    inv[tid] = 1.f / L;
+  }
+  __syncthreads();
+  for (int u0 = tid; u0 < units; u0 += U * kThreads) {
+    int col[U], at[U];
+    f32x4 acc[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int idx = min(u0 + j * kThreads, units - 1);
+      col[j] = idx / UPC;
+      at[j] = o_off + col[j] * D + (idx % UPC) * 4;
+      acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int s0 = 0; s0 < S; s0 += F) {
+      f32x4 os[F][U];
+#pragma unroll
+      for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+          os[f][j] = s0 + f < S ? rd.quad((s0 + f) * rec + at[j]) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        if (s0 + f >= S) break;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const float w = wt[(s0 + f) * C + col[j]];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[j][k] += w * os[f][j][k];
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (u0 + j * kThreads >= units) break;
+      const float x = inv[col[j]];
+      int row, head;
+      col_target(it, rq, a.G, col[j], row, head);
+      store_bf16x4(a.out + ((size_t)row * a.hq + head) * D + (at[j] - o_off - col[j] * D),
+                   acc[j][0] * x, acc[j][1] * x, acc[j][2] * x, acc[j][3] * x);
+    }
+  }
+}
+
 template <int D>
 __device__ void merge_group(const AttnArgs& a, const WorkItem& it, const ReqEntry& rq,
-                            const MergeGroup& grp) {
+                            const MergeGroup& grp, char* lds) {
   const RecordReader rd(reinterpret_cast<const float*>(a.ws + a.ws_partials_off) + grp.ws_off);
   const int C = grp.ncols, S = grp.nsplit;
   const int units = C * (D / 4);
-  if (units >= 4 * kThreads) {
-    // chunk tiles: few splits, many units
-    for (int u0 = 0; u0 < units; u0 += 4 * kThreads) merge_pass<D, 4, 4, 2>(a, it, rq, rd, C, S, u0);
+  static_assert((kLdsMergeSplits + 1) * 128 * 4 <= Cfg<D>::LDS - 16, "weights fit the staging area");
+  if (S <= kLdsMergeSplits) {
+    if (units > 2 * kThreads) merge_lds<D, 4, 4>(a, it, rq, rd, C, S, lds);
+    else merge_lds<D, 2, 8>(a, it, rq, rd, C, S, lds);
   } else {
-    // decode splits and narrow tiles: many splits, few units
+    // very long contexts, or short pieces asked for: any number of splits
     for (int u0 = 0; u0 < units; u0 += kThreads) merge_pass<D, 1, 8, 8>(a, it, rq, rd, C, S, u0);
   }
+}
+
+// The item's merge group (if any).  The plan may lie in host memory, a round
+// trip of over a microsecond: a decode item reads it beside its first loads, a
+// chunk item (whose loop has no registers left for it) once, at its end.
+__device__ __forceinline__ MergeGroup item_group(const AttnArgs& a, const WorkItem& it) {
+  if (it.group < 0) return MergeGroup{1, 0, 0};
+  return reinterpret_cast<const MergeGroup*>(a.plan + a.off_groups)[it.group];
 }
 
 // After this workgroup wrote its partial record (device-scope stores): wait for
@@ -468,12 +549,11 @@ __device__ void merge_group(const AttnArgs& a, const WorkItem& it, const ReqEntr
 // the ticket for the next launch.
 template <int D>
 __device__ void finish_split(const AttnArgs& a, const WorkItem& it, const ReqEntry& rq,
-                             char* lds) {
+                             const MergeGroup& grp, char* lds) {
   // the last word of the kernel's LDS buffer: past the decode merge area, and
   // in staging that is dead once every wave has passed the barrier below
   // (each wave waited for its own copies before leaving its loop)
   int& s_last = *reinterpret_cast<int*>(lds + Cfg<D>::LDS - 16);
-  const MergeGroup grp = reinterpret_cast<const MergeGroup*>(a.plan + a.off_groups)[it.group];
   int* tickets = reinterpret_cast<int*>(a.ws) + kLaunchCounters;
   wait_vm_stores();
   __syncthreads();
@@ -484,7 +564,7 @@ __device__ void finish_split(const AttnArgs& a, const WorkItem& it, const ReqEnt
   }
   __syncthreads();
   if (!s_last) return;
-  merge_group<D>(a, it, rq, grp);
+  merge_group<D>(a, it, rq, grp, lds);
   if (threadIdx.x == 0)
     __hip_atomic_store(&tickets[it.group], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -840,10 +920,6 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
     __syncthreads();
   };
 
-  // The query fragments have landed before the first copy is issued: the
-  // compiler's own waits for them would otherwise count the copies (which it
-  // does not see) and stall on them inside the loop.
-  lds_dma_wait();
   // Block index of the first block holding keys >= u, and the first loop
   // step (a multiple of the stage count) from which the copies are
   // device-scope: at or before the step that fetches that block.
@@ -860,7 +936,10 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
     for (int k = 0; k < S - 1; ++k)
       dma(std::false_type{}, it.key0 + min(k, nb - 1) * 32, lds + k * C::STAGE);
   }
-  vm_wait<kInFlight>();  // blocks 0 and 1 have landed
+  // The query fragments and the first blocks land together.  Nothing may be in
+  // flight here: the compiler's own waits for the fragments would count the
+  // copies (which it does not see) and stall on them inside the loop.
+  lds_dma_wait();
   __syncthreads();
   if (it.key0 + 32 > nvalid) {
     zero_tail(it.key0, lds);
@@ -908,6 +987,7 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
     }
   }
   lds_dma_wait();  // no copy may land after this workgroup has left
+  const MergeGroup grp = item_group(a, it);
 
   // epilogue
 #pragma unroll
@@ -927,7 +1007,6 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
                      o[nt][mt][2] * inv, o[nt][mt][3] * inv);
     }
   } else {
-    const MergeGroup grp = reinterpret_cast<const MergeGroup*>(a.plan + a.off_groups)[it.group];
     const int Cn = grp.ncols;
     float* rec = reinterpret_cast<float*>(a.ws + a.ws_partials_off) + grp.ws_off +
                  (int64_t)it.split * rec_floats(Cn, D);
@@ -945,7 +1024,7 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
         st16_dev(rec + rec_o_off(Cn) + (int64_t)cl * D + mt * 16 + 4 * g,
                  __builtin_bit_cast(u32x4, o[nt][mt]));
     }
-    finish_split<D>(a, it, rq, lds);
+    finish_split<D>(a, it, rq, grp, lds);
   }
 }
 
@@ -1089,6 +1168,7 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
   vm_wait<0>();  // q has landed: the waits below count exactly
   u32x4 v0[MT], v1[MT];
   issue(0, kb_load(0), v0);
+  const MergeGroup grp = item_group(a, it);
   for (int i = 0; i < n2; i += 2) {
     issue(1, kb_load(i + 1), v1);
     wait_loads<kIssue>(v0);
@@ -1115,11 +1195,9 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
   __syncthreads();
 
   float* rec = nullptr;
-  if (it.group >= 0) {
-    const MergeGroup grp = reinterpret_cast<const MergeGroup*>(a.plan + a.off_groups)[it.group];
+  if (it.group >= 0)
     rec = reinterpret_cast<float*>(a.ws + a.ws_partials_off) + grp.ws_off +
           (int64_t)it.split * rec_floats(G, D);
-  }
   for (int idx = tid; idx < G * (D / 4); idx += kThreads) {
     const int col = idx % G;
     const int d0 = (idx / G) * 4;
@@ -1150,7 +1228,7 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
                    acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
     }
   }
-  if (rec) finish_split<D>(a, it, rq, lds);
+  if (rec) finish_split<D>(a, it, rq, grp, lds);
 }
 
 // One attention work item of the plan.

@@ -30,7 +30,7 @@ constexpr int kMaxLen = 1 << 30;
 // CU at half of peak, HBM at 70% of 8 TB/s shared by all CUs.
 constexpr double kMfmaRatePerCu = 2.5e15 / 256.0 * 0.5;
 constexpr double kHbmRate = 8.0e12 * 0.7;
-// A chunk tile's key range is cut only into pieces of at least this many keys:
+// Beside decode rows a chunk tile is cut only into pieces of at least this many keys:
 // each piece costs a partial record of ncols*(D+2) floats written and read back.
 constexpr int kMinChunkSplitKeys = 1024;
 constexpr int kMaxChunkSplits = 16;
@@ -38,6 +38,15 @@ constexpr int kMaxChunkSplits = 16;
 // (its prologue, partial record and share of the merge; measured: three
 // pieces of a 33k-key tile about 6% slower than one).
 constexpr double kSplitCostKeys = 768.0;
+// ... and those that choose_piece_keys cuts, of at least this many (250 tokens on
+// 3001 cached, 32/8 heads: 43 us in pieces of 832, 49 us of 672).
+constexpr int kMinPieceKeys = 512;
+// Batches whose decode rows (at kHbmRate) take under this share of the chunk
+// rows' estimated time: the chunk pieces are chosen by piece_estimate_us.  With
+// more decode work beside them the pieces' records and slots cost the decode
+// items, and the rule by half the makespan measured within 3% of the best fixed
+// length on ten mixed batches.
+constexpr double kPiecesMaxDecodeShare = 0.1;
 // Decode key ranges are cut into equal pieces of about this many keys: long
 // enough that the load latency at the start of an item is amortised over 32
 // blocks per wave, short enough that long and short contexts balance over the
@@ -293,6 +302,109 @@ void order_items(const std::vector<WorkItem>& items, const std::vector<double>& 
   mix(ch, de, tu.mix_order, tu.num_cus, seq);
 }
 
+// Pieces of a tile of kend keys cut at about `keys` keys (0: whole): equal
+// pieces, whole blocks.
+int chunk_nsplit(int kend, int keys) {
+  return keys <= 0 ? 1 : (int)ceil_div(kend, keys);
+}
+// A chunk most of whose keys are its own new rows, with tiles for half of the
+// workgroup slots or more, stays whole: every piece of it would wait for the
+// rows appended in the same launch (2048 tokens on an empty cache, 32/8 heads:
+// 74 us whole, 82 us in pieces of 1536).
+bool stays_whole(int c, int u, int G, int Hkv, int ncu) {
+  return u < c / 2 && ceil_div((int64_t)c * G, kDefaultTileCols) * Hkv >= ncu;
+}
+
+// Estimated microseconds of the chunk rows' launch with tiles cut at `keys`
+// keys: the greedy longest-first schedule of one kv head's pieces on its share
+// of the workgroup slots (two per CU), then the longest merge.  A piece costs
+// 6.5 us and its blocks (0.59 us each alone on a CU, 0.9 us beside another; D =
+// 64 0.73 of that) and, when it writes a partial record, 3.7 us per 128 x 128
+// outputs; the records' bytes move at 2.87 TB/s.  Fitted on MI355X to 25 batches
+// at 12 piece lengths each, within 5% on the mean.  Negative: too many items.
+double piece_estimate_us(const int32_t* q_len, const int32_t* ctx_len, int n, int G, int Hkv, int D,
+                         int ncu, int keys, std::vector<double>* cost, std::vector<double>* slot) {
+  const int64_t slots = 2 * (int64_t)ncu;
+  const double dim = D / 128.0, block_scale = D == 128 ? 1.0 : 0.733;
+  int64_t pieces = 0;
+  for (int i = 0; i < n; ++i) {
+    if (q_len[i] <= 1) continue;
+    const int per = stays_whole(q_len[i], ctx_len[i], G, Hkv, ncu) ? 0 : keys;
+    pieces += ceil_div((int64_t)q_len[i] * G, kDefaultTileCols) *
+              chunk_nsplit(ctx_len[i] + q_len[i], per);
+    if (pieces * Hkv > 4 * slots) return -1.0;
+  }
+  const int64_t items = pieces * Hkv;
+  const double fill = std::min(1.0, std::max(0.0, (double)(items - ncu) / ncu));
+  const double block_us = (0.589 + (0.9 - 0.589) * fill) * block_scale;
+  double record_cols = 0;
+  int max_split = 1;
+  cost->clear();
+  for (int i = 0; i < n; ++i) {
+    const int c = q_len[i], u = ctx_len[i];
+    if (c <= 1) continue;
+    const int per = stays_whole(c, u, G, Hkv, ncu) ? 0 : keys;
+    const int64_t cols = (int64_t)c * G;
+    for (int64_t col0 = 0; col0 < cols; col0 += kDefaultTileCols) {
+      const int ncols = (int)std::min<int64_t>(kDefaultTileCols, cols - col0);
+      const int kend = u + (int)((col0 + ncols - 1) / G) + 1;
+      const int piece = (int)ceil_div(ceil_div(kend, chunk_nsplit(kend, per)), kBlockKeys) * kBlockKeys;
+      const int ns = (int)ceil_div(kend, piece);
+      max_split = std::max(max_split, ns);
+      if (ns > 1) record_cols += (double)ns * ncols;
+      for (int k0 = 0; k0 < kend; k0 += piece)
+        cost->push_back(6.48 + block_us * std::min(piece, kend - k0) / kBlockKeys +
+                        (ns > 1 ? 3.66 * ncols / 128.0 * dim : 0.0));
+    }
+  }
+  std::sort(cost->begin(), cost->end(), std::greater<double>());
+  slot->assign((size_t)std::max<int64_t>(1, slots / Hkv), 0.0);
+  double end = 0.0;
+  for (double t : *cost) {
+    std::pop_heap(slot->begin(), slot->end(), std::greater<double>());
+    slot->back() += t;
+    end = std::max(end, slot->back());
+    std::push_heap(slot->begin(), slot->end(), std::greater<double>());
+  }
+  if (max_split > 1)
+    end += 1.77 + 1.11 * max_split + record_cols * Hkv * D * 4.0 / 2.874e6;
+  return end + 6.96;
+}
+
+// The piece length (0: whole tiles) of a batch whose launch is its chunk rows;
+// -1 where the tiles are too many for the schedule to matter.  Longer pieces
+// first: shorter ones must win by 4%, and two in a row that estimate no better
+// end the search.
+int choose_piece_keys(const int32_t* q_len, const int32_t* ctx_len, int n, int G, int Hkv, int D,
+                      int ncu) {
+  std::vector<double> cost, slot;
+  int longest = 0;
+  for (int i = 0; i < n; ++i)
+    if (q_len[i] > 1) longest = std::max(longest, ctx_len[i] + q_len[i]);
+  struct Found {
+    int keys;
+    double us;
+  } found[9];
+  int nf = 0, worse = 0;
+  double best = 1e300;
+  for (int k : {1, 2, 3, 4, 5, 6, 8, 11, 16}) {  // pieces of the longest tile (kMaxChunkSplits)
+    const int keys = k == 1 ? 0 : (int)ceil_div(ceil_div(longest, k), kBlockKeys) * kBlockKeys;
+    if (k > 1 && keys < kMinPieceKeys) break;
+    const double us = piece_estimate_us(q_len, ctx_len, n, G, Hkv, D, ncu, keys, &cost, &slot);
+    if (us < 0) {
+      if (keys == 0) return -1;
+      break;
+    }
+    found[nf++] = Found{keys, us};
+    worse = us < best ? 0 : worse + 1;
+    best = std::min(best, us);
+    if (worse == 2) break;
+  }
+  for (int k = 0; k < nf; ++k)
+    if (found[k].us <= 1.04 * best) return found[k].keys;
+  return 0;
+}
+
 int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int32_t n,
           const ssa_tuning* tuning, Plan* p) {
   int rc = check_shape(s);
@@ -406,6 +518,14 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
     return (int32_t)p->groups.size() - 1;
   };
 
+  // Chunk batches without (much) decode work: the piece length with the
+  // shortest estimated launch, the longest one within 4% of it; 0: tiles whole.
+  const double decode_time = decode_blocks * kBlockKeys * D * 4.0 / kHbmRate;
+  int piece_keys = -1;  // -1: the rule by half the makespan below
+  if (tu.chunk_split_keys == 0 && tu.tile_cols == kDefaultTileCols && chunk_time_total > 0 &&
+      decode_time < kPiecesMaxDecodeShare * chunk_time_total / ncu)
+    piece_keys = choose_piece_keys(q_len, ctx_len, n, G, Hkv, D, ncu);
+
   // Key splits of a chunk tile (automatic): pieces of at most half the
   // estimated makespan, times `mult`, within [1, kMaxChunkSplits] and pieces of
   // at least kMinChunkSplitKeys keys.
@@ -423,7 +543,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
   // (decode items left out) is simulated for multipliers 1..3, each extra
   // piece charged kSplitCostKeys keys; a larger multiplier must win by 3%.
   int split_mult = 1;
-  if (tu.chunk_split_keys == 0 && makespan > 0) {
+  if (tu.chunk_split_keys == 0 && piece_keys < 0 && makespan > 0) {
     std::vector<double> best_pieces;
     double best = 0.0;
     for (int mult = 1; mult <= 3; ++mult) {
@@ -489,6 +609,8 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
           int nsplit = 1;
           if (tu.chunk_split_keys > 0)
             nsplit = (int)ceil_div(kend, tu.chunk_split_keys);
+          else if (piece_keys >= 0)
+            nsplit = chunk_nsplit(kend, stays_whole(c, u, G, Hkv, ncu) ? 0 : piece_keys);
           else if (makespan > 0)
             nsplit = auto_nsplit(kend, split_mult);
           int piece = (int)ceil_div(ceil_div(kend, nsplit), kBlockKeys) * kBlockKeys;

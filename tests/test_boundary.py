@@ -263,6 +263,27 @@ def test_automatic_chunk_splits_fill_the_last_round():
         assert info.num_chunk_items == 768 * chunk // 1536, chunk
 
 
+@pytest.mark.parametrize("hq,hkv,q,ctx,items", [
+    (32, 8, [250], [3001], 256),            # 64 tiles in 4 pieces
+    (64, 8, [1024], [8192], 512),           # one round of whole tiles
+    (32, 8, [2048], [0], 512),              # its keys are its own new rows: whole
+    (32, 8, [100], [300], 32),              # too short to cut
+    (8, 1, [100], [20000], 112)])           # 7 tiles in 16 pieces
+def test_chunk_pieces_without_decode_rows(hq, hkv, q, ctx, items):
+    """Pieces cover each tile's keys, in whole blocks, at least 512 keys long but
+    for the last one; a mostly decoding batch keeps the rule by its makespan."""
+    shape = shape_of(hq, hkv, 128, np.array(q, np.int32), np.array(ctx, np.int32))
+    blob, info = ssa.ssa_plan(shape, q, ctx)
+    assert info.num_chunk_items == items
+    it = parse(blob)[2]
+    for col0 in np.unique(it["col0"]):
+        for h in range(hkv):
+            t = np.sort(it[(it["col0"] == col0) & (it["kvh"] == h)], order="key0")
+            assert t["key0"][0] == 0 and np.array_equal(t["key0"][1:], t["key1"][:-1])
+            assert (t["key0"] % 32 == 0).all()
+            assert len(t) == 1 or (t["key1"] - t["key0"])[:-1].min() >= 512
+
+
 def test_plan_is_deterministic():
     q_len = np.array([300, 1, 1, 1], np.int32)
     ctx_len = np.array([0, 5, 900, 40], np.int32)

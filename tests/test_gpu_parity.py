@@ -488,3 +488,29 @@ def test_fused_wait_time_out_is_reported_and_every_workgroup_exits(torch_dev):
     db.plan(ssa.make_tuning())
     db.step_fused()
     assert db.status() == 0 and not db.launch_words().any()
+
+
+@pytest.mark.parametrize("hq,hkv,d,tile,splits", [
+    (8, 2, 128, 128, 2), (8, 2, 128, 128, 5), (8, 1, 128, 128, 16), (8, 1, 128, 128, 17),
+    (28, 4, 128, 64, 4), (8, 8, 64, 128, 15), (8, 8, 64, 32, 17)])
+def test_merges_of_many_splits(torch_dev, hq, hkv, d, tile, splits):
+    """Chunk tiles and decode rows cut in so many pieces: rounds of four or eight
+    splits with remainders, and either side of the 16 splits whose weights one
+    pass holds; full and narrow last tiles."""
+    from paper_2606_05933_amd import ssa, workload
+    u = 32 * splits - 60
+    c = 37 if hq // hkv < 8 else 18
+    b = workload.make_batch(workload.Shape(hq, hkv, d), [c, 1, 1], [u, u + c - 1, 5], seed=splits,
+                            name=f"splits_{splits}")
+    t = ssa.make_tuning(chunk_tile_cols=tile, chunk_split_keys=32, decode_split_keys=32)
+    full_parity(b, t)
+
+
+def test_default_pieces_of_short_chunks_on_long_prefixes(torch_dev):
+    """Chunk batches without decode rows, at sizes whose tiles the planner cuts."""
+    from paper_2606_05933_amd import workload
+    for shape, c, u in ((workload.Shape(32, 8, 128), [50], [3001]),
+                        (workload.Shape(8, 1, 128), [30], [9000]),
+                        (workload.Shape(28, 4, 128), [9, 64], [4000, 700])):
+        b = workload.make_batch(shape, c, u, seed=3, name="pieces")
+        full_parity(b)
