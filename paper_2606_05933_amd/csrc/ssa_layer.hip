@@ -2,7 +2,7 @@
 //
 // ssa_rope_append: for each append segment of the plan (consecutive new
 // tokens of one request inside one page, at most 16), workgroups of 8 heads
-// each.  A rotating workgroup rotates 8 of the segment's query and key heads
+// each; for a decode request's single row, one workgroup for all its heads.  A rotating workgroup rotates 8 of the segment's query and key heads
 // (rotate-half pairs (i, i + D/2), cos/sin from the position's row of the
 // table) and writes the queries to q_out and the keys to their slots of the
 // key page (slot-major rows); a value workgroup stages 8 value heads' rows in
@@ -56,12 +56,23 @@ struct RopeArgs {
   uint16_t* vc;
   const int32_t* bt;
   int hq, hkv, maxp;
+  int grouped_segs;  // segments run by head groups; the others are single rows
 };
 
-// Heads per workgroup: blockIdx.y < rot_groups rotates query/key heads
-// 8 y .. 8 y + 7 (of the Hq + Hkv rotated ones); the others copy value heads.
+// Heads per workgroup of a grouped segment: group y < rot_groups rotates
+// query/key heads 8 y .. 8 y + 7 (of the Hq + Hkv rotated ones); the others copy
+// value heads.
 constexpr int kHeadGroup = 8;
+constexpr int kSingleMaxHeads = 16 * kHeadGroup;  // rotated heads of one row per workgroup
 
+// Latency bounds it at small T: launch, the segment's record (in host memory
+// where the plan is), the rows, the stores.  A decode row has 1/16 of a chunk
+// segment's work per head, so all its heads share one workgroup: a sixth of the
+// workgroups, and of the reads of the plan over the bus (32/8 heads, plan in
+// host memory: 128 rows 8.4 -> 7.1 us, and 512 chunk tokens with them 11.9 ->
+// 9.3).  Segment-major ids put a segment's head groups, which share its cache
+// lines of the table and the rows, side by side (2048 chunk tokens, plan on the
+// device: 13.6 -> 10.5 us; bytes at the copy rate 10).
 template <int D>
 __global__ __launch_bounds__(kLayerThreads) void rope_append_kernel(RopeArgs a) {
   constexpr int HALF = D / 2, UPH = HALF / 8;     // 8-pair units per head
@@ -71,16 +82,60 @@ __global__ __launch_bounds__(kLayerThreads) void rope_append_kernel(RopeArgs a) 
   constexpr int TU = HG * 2 * D / kLayerThreads;     // value half rows per thread
   __shared__ __attribute__((aligned(16))) uint16_t vt[HG * 16 * D];  // [head][row][D]
   const PlanHeader* hdr = reinterpret_cast<const PlanHeader*>(a.plan);
-  const AppendSeg sg = reinterpret_cast<const AppendSeg*>(a.plan + a.off_segments)[blockIdx.x];
+  // workgroups of the grouped segments (segment-major), then one per single row
+  const int nrot = a.hq + a.hkv, rot_groups = (nrot + HG - 1) / HG;
+  const int groups = rot_groups + (a.hkv + HG - 1) / HG, wg = (int)blockIdx.x;
+  const bool single = wg >= a.grouped_segs * groups;
+  const int seg = single ? a.grouped_segs + (wg - a.grouped_segs * groups) : wg / groups;
+  const int group = single ? 0 : wg % groups;
+  const AppendSeg sg = reinterpret_cast<const AppendSeg*>(a.plan + a.off_segments)[seg];
   if (hdr->magic != kPlanMagic || hdr->hash != a.hash) return;
   const int n = sg.n, slot0 = sg.pos0 % 16, tid = threadIdx.x;
   const size_t stride = (size_t)(a.hq + 2 * a.hkv) * D;
   const size_t pb = (size_t)a.bt[(size_t)sg.req * a.maxp + sg.pos0 / 16] * a.hkv * 16 * D;
-  const int nrot = a.hq + a.hkv, rot_groups = (nrot + HG - 1) / HG;
-  if ((int)blockIdx.y < rot_groups) {
+  if (single) {
+    // one row: its value heads' chunks (slot by slot into the dim-major page)
+    // and every query and key head's units, all loads first
+    const int nu = nrot * UPH, nv = a.hkv * (D / 8);
+    const uint16_t* row = a.qkv + (size_t)sg.row0 * stride;
+    u32x4 x1[RU], x2[RU], v[RU];
+#pragma unroll
+    for (int j = 0; j < RU; ++j) {
+      const int idx = tid + j * kLayerThreads;
+      if (idx < nu) {
+        const uint16_t* src = row + (size_t)(idx / UPH) * D + (idx % UPH) * 8;
+        x1[j] = ld16(src);
+        x2[j] = ld16(src + HALF);
+      }
+      if (idx < nv) v[j] = ld16(row + (size_t)nrot * D + idx * 8);
+    }
+#pragma unroll
+    for (int j = 0; j < RU; ++j) {
+      const int idx = tid + j * kLayerThreads;
+      if (idx < nu) {
+        const int h = idx / UPH, i = (idx % UPH) * 8;
+        u32x4 o1, o2;
+        rotate8(x1[j], x2[j], a.cos_sin + (size_t)sg.pos0 * D, HALF, i, &o1, &o2);
+        uint16_t* dst = h < a.hq ? a.q_out + ((size_t)sg.row0 * a.hq + h) * D
+                                 : a.kc + pb + (size_t)(h - a.hq) * 16 * D + (size_t)slot0 * D;
+        st16(dst + i, o1);
+        st16(dst + HALF + i, o2);
+      }
+      if (idx < nv) {
+        uint16_t* dst = a.vc + pb + (size_t)idx * 8 * 16 + slot0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          dst[(2 * k) * 16] = (uint16_t)v[j][k];
+          dst[(2 * k + 1) * 16] = (uint16_t)(v[j][k] >> 16);
+        }
+      }
+    }
+    return;
+  }
+  if (group < rot_groups) {
     // query and key heads h0 .. h0 + nh - 1: units (row, head, 8 pairs); all
     // loads first, then the rotations and stores
-    const int h0 = blockIdx.y * HG, nh = min(HG, nrot - h0);
+    const int h0 = group * HG, nh = min(HG, nrot - h0);
     const int nu = n * nh * UPH;
     u32x4 x1[RU], x2[RU];
 #pragma unroll
@@ -109,7 +164,7 @@ __global__ __launch_bounds__(kLayerThreads) void rope_append_kernel(RopeArgs a) 
     return;
   }
   // value heads h0 .. h0 + nh - 1: rows to LDS, then 8-slot half rows of one dim
-  const int h0 = ((int)blockIdx.y - rot_groups) * HG, nh = min(HG, a.hkv - h0);
+  const int h0 = (group - rot_groups) * HG, nh = min(HG, a.hkv - h0);
   const int nv = n * nh * (D / 8);
   u32x4 v[VU];
 #pragma unroll
@@ -172,10 +227,15 @@ int ssa_rope_append(const ssa_shape* shape, const void* plan_host, const void* p
   if (h->num_segments == 0) return SSA_OK;
   if (!qkv || !cos_sin || !q_out || !k_cache || !v_cache || !block_table) return SSA_ERR_NULL;
   (void)hipGetLastError();
+  // A single row's rotated units must fit the units one workgroup holds (128
+  // heads); the plan lists the segments of chunk requests first.
+  const int32_t grouped =
+      h->hq + h->hkv <= kSingleMaxHeads ? h->num_chunk_segments : h->num_segments;
   RopeArgs a{static_cast<const uint8_t*>(plan_dev), h->hash, h->off_segments, qkv, cos_sin,
-             q_out, k_cache, v_cache, block_table, h->hq, h->hkv, h->max_pages_per_req};
-  const dim3 grid(h->num_segments, (h->hq + h->hkv + kHeadGroup - 1) / kHeadGroup +
-                                       (h->hkv + kHeadGroup - 1) / kHeadGroup);
+             q_out, k_cache, v_cache, block_table, h->hq, h->hkv, h->max_pages_per_req, grouped};
+  const int32_t groups = (h->hq + h->hkv + kHeadGroup - 1) / kHeadGroup +
+                         (h->hkv + kHeadGroup - 1) / kHeadGroup;
+  const dim3 grid(grouped * groups + (h->num_segments - grouped));
   if (h->head_dim == 128)
     hipLaunchKernelGGL(rope_append_kernel<128>, grid, dim3(kLayerThreads), 0,
                        static_cast<hipStream_t>(stream), a);

@@ -94,6 +94,16 @@ def test_rope_append_matches_the_oracle(torch_dev, case):
     run_case(torch_dev, hq, hkv, d, cu, seed=case)
 
 
+@pytest.mark.parametrize("hq,hkv,d,cu", [
+    (64, 64, 128, [(1, 15), (1, 16), (2, 3)]),    # 128 rotated heads: one row fills a workgroup
+    (64, 64, 64, [(1, 0), (1, 31), (1, 100)]),
+    (128, 16, 128, [(1, 7), (3, 14), (1, 40)]),   # more: single rows go by head groups
+    (1, 1, 64, [(1, 5), (1, 63)]),
+    (28, 4, 128, [(1, 9)] * 40)])
+def test_rope_append_single_rows(torch_dev, hq, hkv, d, cu):
+    run_case(torch_dev, hq, hkv, d, cu, seed=hq + d)
+
+
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_rope_append_then_attention(torch_dev, case):
     from dense_ref import to_bf16
