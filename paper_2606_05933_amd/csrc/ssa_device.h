@@ -63,4 +63,29 @@ __device__ __forceinline__ void vm_wait() {
 }
 __device__ __forceinline__ void lds_dma_wait() { vm_wait<0>(); }
 
+// Split partials that cross workgroups (and XCDs, whose L2s are not coherent with
+// each other) are written through to the device coherence point: 16-byte buffer
+// stores with the device-coherent cache policy (sc1), the instruction of a
+// device-scope store.  A wave's store then covers whole lines; as two 8-byte
+// device-scope atomics, each instruction wrote half of every 16 bytes.
+// us with 8-byte and with 16-byte stores: 250 rows on 3001 cached (32/8 heads, key
+// ranges in 4 pieces) 42.0 and 39.2; a Llama-3-8B layer of 640 tokens (split
+// projections) 498.5 and 489; of 128 decodes 274.3 and 272.2.
+// base is wave-uniform; offsets are bytes from it.
+constexpr int kCachePolicySc1 = 16;
+struct PartWriter {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ explicit PartWriter(float* base) {
+    const uint64_t b = (uint64_t)(uintptr_t)base;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<float*>((uintptr_t)(((uint64_t)hi << 32) | lo)), (short)0, 0x7fffffff,
+        0x00020000);
+  }
+  __device__ void operator()(int byte_off, u32x4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, byte_off, 0, kCachePolicySc1);
+  }
+};
+
 }  // namespace ssa_dev

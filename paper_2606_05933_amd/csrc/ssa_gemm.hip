@@ -58,23 +58,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 // From here on 7 rows of 2 K bytes and a chunk pass 32 bits: 64-bit addresses.
 constexpr int kWideK = 1 << 28;
 
-// Split partials cross workgroups and XCDs (whose L2s are not coherent with
-// each other): device-scope 8-byte stores, device-coherent loads (below), a
-// device-scope ticket.
-__device__ __forceinline__ void st16_dev(float* p, f32x4 v) {
-  uint64_t* q = reinterpret_cast<uint64_t*>(p);
-  const uint64_t lo = (uint64_t)__float_as_uint(v[0]) | ((uint64_t)__float_as_uint(v[1]) << 32);
-  const uint64_t hi = (uint64_t)__float_as_uint(v[2]) | ((uint64_t)__float_as_uint(v[3]) << 32);
-  __hip_atomic_store(q, lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(q + 1, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // Reads of the partials: 16-byte buffer loads with the device-coherent cache
 // policy (sc1), the instruction of a device-scope load, so they do not hit a
 // stale line of this XCD's L2.  Being plain loads to the compiler, they are
 // issued back to back and waited for where a value is used (device-scope
 // atomic loads would be serialised).  Offsets are bytes from the tile's first
 // partial; a read past num_records would return zeros, never fault.
-constexpr int kCachePolicySc1 = 16;
 struct PartReader {
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ explicit PartReader(const float* base)
@@ -294,12 +283,13 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
     int& s_last = *reinterpret_cast<int*>(lds);
     float* const parts = a.part + (size_t)tile * a.splits * C::kTileFloats;
     const int mine = w * (TM * TN * 256) + lane * 4;
+    const PartWriter wr(parts + (size_t)split * C::kTileFloats);
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt)
       if (mt < nmt)
 #pragma unroll
         for (int nt = 0; nt < TN; ++nt)
-          st16_dev(parts + (size_t)split * C::kTileFloats + mine + (mt * TN + nt) * 256, acc[mt][nt]);
+          wr((mine + (mt * TN + nt) * 256) * 4, __builtin_bit_cast(u32x4, acc[mt][nt]));
     vm_wait<0>();     // this thread's device-scope stores have completed
     __syncthreads();  // everyone's have, and the ring is free
     // the tile's 4-bit counter: tile % 64 names the word, tile / 64 the nibble

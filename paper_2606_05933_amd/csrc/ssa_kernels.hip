@@ -354,7 +354,6 @@ __device__ __forceinline__ void wait_vm_stores() { __builtin_amdgcn_s_waitcnt(0x
 // the compiler, many are issued before the first wait (device-scope atomic
 // loads are issued one split at a time).  Offsets are bytes from the group's
 // first record.
-constexpr int kCachePolicySc1 = 16;
 struct RecordReader {
   __amdgpu_buffer_rsrc_t rsrc;
   __device__ explicit RecordReader(const float* base)
@@ -1010,19 +1009,20 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
     const int Cn = grp.ncols;
     float* rec = reinterpret_cast<float*>(a.ws + a.ws_partials_off) + grp.ws_off +
                  (int64_t)it.split * rec_floats(Cn, D);
+    const PartWriter wr(rec);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int col = wc0 + nt * 16 + r16;
       if (col >= colend) continue;
       const int cl = col - it.col0;
+      const int at = (int)(rec_o_off(Cn) + (int64_t)cl * D + 4 * g) * 4;
       if (g == 0) {
         st_dev(rec + cl, cs[nt].m);
         st_dev(rec + Cn + cl, cs[nt].l);
       }
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)  // 16-byte aligned, as records and o rows are
-        st16_dev(rec + rec_o_off(Cn) + (int64_t)cl * D + mt * 16 + 4 * g,
-                 __builtin_bit_cast(u32x4, o[nt][mt]));
+        wr(at + mt * 64, __builtin_bit_cast(u32x4, o[nt][mt]));
     }
     finish_split<D>(a, it, rq, grp, lds);
   }
@@ -1198,6 +1198,7 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
   if (it.group >= 0)
     rec = reinterpret_cast<float*>(a.ws + a.ws_partials_off) + grp.ws_off +
           (int64_t)it.split * rec_floats(G, D);
+  const PartWriter wr(rec);  // used only where rec is set
   for (int idx = tid; idx < G * (D / 4); idx += kThreads) {
     const int col = idx % G;
     const int d0 = (idx / G) * 4;
@@ -1219,9 +1220,9 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
         st_dev(rec + col, M);
         st_dev(rec + G + col, L);
       }
-      st16_dev(rec + rec_o_off(G) + (int64_t)col * D + d0,  // 16-byte aligned
-               u32x4{__builtin_bit_cast(uint32_t, acc[0]), __builtin_bit_cast(uint32_t, acc[1]),
-                     __builtin_bit_cast(uint32_t, acc[2]), __builtin_bit_cast(uint32_t, acc[3])});
+      wr((int)(rec_o_off(G) + (int64_t)col * D + d0) * 4,  // 16-byte aligned
+         u32x4{__builtin_bit_cast(uint32_t, acc[0]), __builtin_bit_cast(uint32_t, acc[1]),
+               __builtin_bit_cast(uint32_t, acc[2]), __builtin_bit_cast(uint32_t, acc[3])});
     } else {
       const float inv = 1.f / L;
       store_bf16x4(a.out + ((size_t)rq.q_start * a.hq + it.kvh * G + col) * D + d0,
@@ -1457,6 +1458,7 @@ __device__ __forceinline__ void decode_stream_item(const AttnArgs& a, const Work
     rec = reinterpret_cast<float*>(a.ws + a.ws_partials_off) + grp.ws_off +
           (int64_t)it.split * rec_floats(G, D);
   }
+  const PartWriter wr(rec);  // used only where rec is set
   // lane (g, r16) holds dims 32w + 16mt + 4g .. +3 of column r16
   if (r16 < G) {
     if (rec) {
@@ -1466,8 +1468,8 @@ __device__ __forceinline__ void decode_stream_item(const AttnArgs& a, const Work
       }
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
-        st16_dev(rec + rec_o_off(G) + (int64_t)r16 * D + 32 * w + 16 * mt + 4 * g,
-                 __builtin_bit_cast(u32x4, o[mt]));
+        wr((int)(rec_o_off(G) + (int64_t)r16 * D + 32 * w + 16 * mt + 4 * g) * 4,
+           __builtin_bit_cast(u32x4, o[mt]));
     } else {
       const float inv = 1.f / l;
 #pragma unroll
