@@ -1264,7 +1264,9 @@ __global__ __launch_bounds__(kThreads, 2) void mixed_attention_kernel(AttnArgs a
 //
 // The decode items of ssa_append_attention_streams, in a kernel of their own
 // that runs beside the chunk rows' launch.  A CU holds two chunk workgroups
-// (two waves of 216 registers per SIMD, 64 KB of LDS each); this kernel is
+// (two waves of 216 registers per SIMD, 64 KB of LDS each; with 217, allocated as
+// 224, a decode workgroup no longer fits beside them and the 1024-token step at
+// the 70B shape took 1451 us, not 1345); this kernel is
 // built to fit in what they leave, 80 registers per lane and 32 KB, so that one
 // of its workgroups runs on every CU as a third resident workgroup and streams
 // the decode rows' K/V while the chunk tiles compute.
