@@ -39,7 +39,8 @@ constexpr int kMaxChunkSplits = 16;
 // pieces of a 33k-key tile about 6% slower than one).
 constexpr double kSplitCostKeys = 768.0;
 // ... and those that choose_piece_keys cuts, of at least this many (250 tokens on
-// 3001 cached, 32/8 heads: 43 us in pieces of 832, 49 us of 672).
+// 3001 cached, 32/8 heads: 43 us in pieces of 832, 49 us of 672; 39 us in pieces
+// of 832 since the records are written with 16-byte stores).
 constexpr int kMinPieceKeys = 512;
 // Batches whose decode rows (at kHbmRate) take under this share of the chunk
 // rows' estimated time: the chunk pieces are chosen by piece_estimate_us.  With
@@ -321,7 +322,8 @@ bool stays_whole(int c, int u, int G, int Hkv, int ncu) {
 // 6.5 us and its blocks (0.59 us each alone on a CU, 0.9 us beside another; D =
 // 64 0.73 of that) and, when it writes a partial record, 3.7 us per 128 x 128
 // outputs; the records' bytes move at 2.87 TB/s.  Fitted on MI355X to 25 batches
-// at 12 piece lengths each, within 5% on the mean.  Negative: too many items.
+// at 12 piece lengths each, within 5% on the mean, when records were written with
+// 8-byte stores: a split launch now takes up to 7% less.  Negative: too many items.
 double piece_estimate_us(const int32_t* q_len, const int32_t* ctx_len, int n, int G, int Hkv, int D,
                          int ncu, int keys, std::vector<double>* cost, std::vector<double>* slot) {
   const int64_t slots = 2 * (int64_t)ncu;
