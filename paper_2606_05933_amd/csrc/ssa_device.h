@@ -37,21 +37,25 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // is inline assembly, so the compiler's memory-counter tracking does not make
 // reads of other LDS buffers wait for it; every reader of the destination
 // waits explicitly (vm_wait, then the barrier that publishes the buffer).
+// The copy reads M0, and on this architecture a scalar write of M0 and a
+// global -> LDS load that reads it need one wait state between them.  The
+// compiler inserts it for its own instructions but does not look inside inline
+// assembly, so the s_nop is part of every copy (here and in ssa_gemm.hip).
 // COHERENT: a device-scope read (sc1), for rows written in the same launch.
 template <bool COHERENT = false>
 __device__ __forceinline__ void dma16(const void* g, const char* l) {
   const uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)l;
   if (COHERENT)
-    asm volatile("global_load_lds_dwordx4 %0, off sc1" ::"v"(g), "{m0}"(a) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1" ::"v"(g), "{m0}"(a) : "memory");
   else
-    asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(a) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(a) : "memory");
 }
 
 // dma16 with the non-temporal hint (nt), for rows a workgroup reads once: they
 // should not displace what the caches hold for other workgroups.
 __device__ __forceinline__ void dma16_stream(const void* g, const char* l) {
   const uint32_t a = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)l;
-  asm volatile("global_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(a) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "{m0}"(a) : "memory");
 }
 
 // s_waitcnt vmcnt(N): all but this wave's N most recent vector-memory

@@ -186,10 +186,12 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
     if (MODE == kWide)
       dma16(src[r] + koff, dst);
     else if (MODE == kStream && r * C::kWaves + w >= BM / 8)
-      asm volatile("global_load_lds_dwordx4 %0, %1 nt" ::"v"(off[r]), "s"(src[r] + koff), "{m0}"(l)
+      asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off[r]),
+                   "s"(src[r] + koff), "{m0}"(l)
                    : "memory");
     else
-      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off[r]), "s"(src[r] + koff), "{m0}"(l)
+      asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off[r]),
+                   "s"(src[r] + koff), "{m0}"(l)
                    : "memory");
   };
   auto block_off = [&](int i) {  // byte offset of the tile's i-th K block along a row
