@@ -1177,7 +1177,9 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
     wait_loads<kIssue>(v1);
     compute(1, kb_of(i + 1), v1);
   }
-  vm_wait<0>();  // the last (unused) copies have landed before LDS is reused
+  // The last (unused) key copies have landed before LDS is reused, and the last
+  // value loads before their registers are.
+  wait_loads<0>(v0);
   l_run = wave_sum_cols(l_run);
   // merge the 4 waves through LDS: per wave m[16], l[16], o[D][16] (over the
   // staging area: every wave has left its loop)
