@@ -124,7 +124,9 @@ typedef struct ssa_layer_weights {
  * Workspace bytes of ssa_layer_forward for this plan: the activations of the
  * plan's T tokens, the attention workspace of the plan, the linear layers'
  * split workspace.  The workspace must be zero before its first use (a zeroed
- * allocation); the counters in it are zero again after every call.
+ * allocation).  After that it serves calls with any plans it is large enough for,
+ * one after another: each call clears the split tickets where its own plan has
+ * them, in its first launch.
  */
 int ssa_layer_workspace_size(const ssa_shape* shape, const void* plan_host,
                              const ssa_layer_weights* w, size_t* ws_bytes);

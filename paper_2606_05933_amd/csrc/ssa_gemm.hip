@@ -47,6 +47,7 @@
 
 #include "../../include/ssa_layer.h"
 #include "ssa_device.h"
+#include "ssa_layer_internal.h"
 
 namespace {
 using namespace ssa_dev;
@@ -375,12 +376,20 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
   }
 }
 
-// RMSNorm: one workgroup per row, up to 4 16-byte chunks per thread.
+// RMSNorm: one workgroup per row, up to 4 16-byte chunks per thread.  `clear`:
+// words that the launches behind it on the stream need to be zero (a layer's
+// split tickets), spread over all threads.
 constexpr int kNormChunks = 4;
 __global__ __launch_bounds__(kNormThreads) void rms_norm_kernel(const uint16_t* x, const uint16_t* wt,
-                                                            uint16_t* out, int n, float eps) {
+                                                            uint16_t* out, int n, float eps,
+                                                            ssa::ClearWords clear) {
   __shared__ float s_part[kNormThreads / 64];
   const int tid = threadIdx.x;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    for (int64_t i = (int64_t)blockIdx.x * kNormThreads + tid; i < clear.n[c];
+         i += (int64_t)gridDim.x * kNormThreads)
+      clear.at[c][i] = 0;
   const uint16_t* row = x + (size_t)blockIdx.x * n;
   u32x4 v[kNormChunks];
   float ss = 0.f;
@@ -452,7 +461,7 @@ constexpr int kCus = 256;
 // Split tickets: a 4-bit counter per tile in the workspace's first 256 bytes,
 // whatever the shape, so that products of different shapes can share a
 // workspace (the partials of one never lie where another's tickets are).
-constexpr size_t kTicketBytes = 256;
+constexpr size_t kTicketBytes = ssa::kLinearTicketBytes;
 constexpr int kMaxSplitTiles = (int)kTicketBytes * 2, kMaxSplits = 15;
 
 // cfg's tiles in (up to) s K splits; one where the tickets do not suffice.
@@ -588,6 +597,22 @@ int check_linear(int32_t m, int32_t n, int32_t k, int32_t epilogue) {
 
 }  // namespace
 
+namespace ssa {
+
+int rms_norm(int32_t m, int32_t n, const uint16_t* x, const uint16_t* weight, float eps,
+             uint16_t* out, const ClearWords& clear, void* stream) {
+  if (m < 0 || n <= 0 || n % 8 || n > kNormThreads * 8 * kNormChunks || !(eps >= 0.f))
+    return SSA_ERR_ARG;
+  if (m == 0) return SSA_OK;
+  if (!x || !weight || !out) return SSA_ERR_NULL;
+  (void)hipGetLastError();
+  hipLaunchKernelGGL(rms_norm_kernel, dim3(m), dim3(kNormThreads), 0, static_cast<hipStream_t>(stream),
+                     x, weight, out, n, eps, clear);
+  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+}
+
+}  // namespace ssa
+
 extern "C" {
 
 int ssa_linear_workspace_size(int32_t m, int32_t n, int32_t k, size_t* ws_bytes) {
@@ -613,14 +638,7 @@ int ssa_linear(int32_t m, int32_t n, int32_t k, int32_t epilogue, const uint16_t
 
 int ssa_rms_norm(int32_t m, int32_t n, const uint16_t* x, const uint16_t* weight, float eps,
                  uint16_t* out, void* stream) {
-  if (m < 0 || n <= 0 || n % 8 || n > kNormThreads * 8 * kNormChunks || !(eps >= 0.f))
-    return SSA_ERR_ARG;
-  if (m == 0) return SSA_OK;
-  if (!x || !weight || !out) return SSA_ERR_NULL;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(rms_norm_kernel, dim3(m), dim3(kNormThreads), 0, static_cast<hipStream_t>(stream),
-                     x, weight, out, n, eps);
-  return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
+  return ssa::rms_norm(m, n, x, weight, eps, out, ssa::ClearWords{}, stream);
 }
 
 }  // extern "C"

@@ -8,6 +8,7 @@
 #include <cmath>
 
 #include "../../include/ssa_layer.h"
+#include "ssa_layer_internal.h"
 #include "ssa_plan_format.h"
 
 namespace ssa {
@@ -19,8 +20,11 @@ using namespace ssa;
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Byte offsets of the regions of the layer workspace.  The attention and
-// linear workspaces (whose counters must stay zero at rest) come first.
+// Byte offsets of the regions of the layer workspace.  Where the split tickets
+// of attention and of the linear layers lie depends on the plan, so another
+// plan's call may have left records or activations there: the first launch
+// clears them.  The attention workspace comes first, so its launch counters and
+// status word lie at the same place for every plan, and are left alone.
 struct LayerWs {
   size_t attn, gemm, xn, qkv, q, a, h, act, total;
   size_t attn_bytes, gemm_bytes;
@@ -127,7 +131,12 @@ int ssa_layer_forward(const ssa_shape* shape, const void* plan_host, const void*
   const int32_t hid = w->hidden, qd = h->hq * h->head_dim;
   const int32_t nqkv = (h->hq + 2 * h->hkv) * h->head_dim;
 
-  if ((rc = ssa_rms_norm(t, hid, x, w->attn_norm, w->eps, xn, stream))) return rc;
+  const size_t counters = kLaunchCounters * sizeof(uint32_t);
+  const ClearWords tickets = {
+      {reinterpret_cast<uint32_t*>(ws + l.attn + counters), static_cast<uint32_t*>(gws)},
+      {((int64_t)h->ws_partials_off - (int64_t)counters) / 4,
+       l.gemm_bytes > 0 ? (int64_t)(kLinearTicketBytes / 4) : 0}};
+  if ((rc = rms_norm(t, hid, x, w->attn_norm, w->eps, xn, tickets, stream))) return rc;
   if ((rc = ssa_linear(t, nqkv, hid, SSA_EPILOGUE_NONE, xn, w->w_qkv, nullptr, qkv, gws,
                        l.gemm_bytes, stream)))
     return rc;

@@ -211,6 +211,44 @@ def test_layer_forward_matches_the_oracle(torch_dev, case):
     assert np.all(verr <= 2.0 ** -6 * np.abs(vr[vfin]) + 2.0 ** -10)
 
 
+def test_layer_forward_serves_plans_one_after_another_from_one_workspace(torch_dev):
+    """Where a plan's split tickets lie in the layer workspace depends on the plan:
+    a call finds records, activations or projections' partial tiles of the calls
+    before it there, and must still write every output."""
+    from paper_2606_05933_amd import ssa, workload
+    from paper_2606_05933_amd.device import DeviceBatch, bits_of
+    torch = torch_dev
+    hidden, inter, hq, hkv, d = 512, 4096, 8, 2, 64
+    w = workload.layer_weights(70, hidden, inter, hq, hkv, d)
+    lw = ssa.LayerWeights(w, hq, hkv, d, max_position=9000)
+    plans = [[(1, 8000)] * 3, [(200, 0)], [(1, 40)] * 130, [(90, 4000), (1, 3)],
+             [(1, 8500)] * 20, [(3, 5), (1, 7)]]
+    batches = []
+    for i, cu in enumerate(plans):
+        b = workload.make_batch(workload.Shape(hq, hkv, d), [c for c, _ in cu], [u for _, u in cu],
+                                seed=70 + i, spare_pages=3, name="layer")
+        db = DeviceBatch(b, ssa.make_tuning(chunk_split_keys=64, decode_split_keys=256))
+        x = torch.from_numpy(workload.normal_bf16((b.num_tokens, hidden), 80 + i).view(np.int16))
+        batches.append((db, x.cuda().view(torch.bfloat16)))
+    sizes = [ssa.layer_workspace_size(db.shape, db.plan_host, lw) for db, _ in batches]
+
+    def layer(db, x, ws):
+        out = torch.full_like(x, float("nan"))
+        ssa.layer_forward(db.shape, db.plan_host, db.plan_dev, lw, x, out, db.k_cache, db.v_cache,
+                          db.block_table, ws)
+        torch.cuda.synchronize()
+        return bits_of(out)
+
+    alone = [layer(db, x, torch.zeros(n, dtype=torch.uint8, device="cuda"))
+             for (db, x), n in zip(batches, sizes)]
+    shared = torch.zeros(max(sizes), dtype=torch.uint8, device="cuda")
+    for rnd in range(2):
+        for i in (range(len(plans)) if rnd == 0 else reversed(range(len(plans)))):
+            say(f"[gpu layer shared workspace] round {rnd} plan {i} {plans[i][:2]}")
+            db, x = batches[i]
+            assert np.array_equal(layer(db, x, shared), alone[i]), plans[i][:2]
+
+
 def test_layer_forward_replays_from_a_hip_graph(torch_dev):
     """ssa_layer_forward captured in a HIP graph (eight launches, no allocation,
     no memset) replays to the eager result, bit for bit, with eager work and
