@@ -1839,7 +1839,6 @@ int launch_append_attention(const PlanHeader* h, AttnArgs& a, AppendArgs& ap, vo
 // One copy per GPU (held until the process ends); every call on a GPU shares
 // it.  In host code the name is a stand-in, not a device address: the
 // per-device address comes from hipGetSymbolAddress.
-constexpr size_t kScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 namespace {
@@ -1950,7 +1949,7 @@ int ssa_append_attention_static(const ssa_shape* shape, const void* plan_host,
   // workspace of its size at a placeholder address until it is resolved
   int rc = check_plan(shape, plan_host, &h);
   if (rc) return rc;
-  if (h->ws_bytes > (int64_t)kScratchBytes) return SSA_ERR_WORKSPACE;
+  if (h->ws_bytes > kScratchBytes) return SSA_ERR_WORKSPACE;
   rc = append_attention_args(shape, plan_host, plan_dev, q, k_new, v_new, k_cache, v_cache,
                              block_table, out, reinterpret_cast<void*>(kScratchBytes),
                              kScratchBytes, &h, &a, &ap);

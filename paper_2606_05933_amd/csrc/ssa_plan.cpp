@@ -316,73 +316,89 @@ bool stays_whole(int c, int u, int G, int Hkv, int ncu) {
   return u < c / 2 && ceil_div((int64_t)c * G, kDefaultTileCols) * Hkv >= ncu;
 }
 
-// Estimated microseconds of the chunk rows' launch with tiles cut at `keys`
-// keys: the greedy longest-first schedule of one kv head's pieces on its share
-// of the workgroup slots (two per CU), then the longest merge.  A piece costs
-// 6.5 us and its blocks (0.59 us each alone on a CU, 0.9 us beside another; D =
-// 64 0.73 of that) and, when it writes a partial record, 3.7 us per 128 x 128
-// outputs; the records' bytes move at 2.87 TB/s.  Fitted on MI355X to 25 batches
-// at 12 piece lengths each, within 5% on the mean, when records were written with
-// 8-byte stores: a split launch now takes up to 7% less.  Negative: too many items.
-double piece_estimate_us(const int32_t* q_len, const int32_t* ctx_len, int n, int G, int Hkv, int D,
-                         int ncu, int keys, std::vector<double>* cost, std::vector<double>* slot) {
+// A chunk tile of one kv head; `whole`: its chunk stays whole (stays_whole).
+struct ChunkTile {
+  int kend, ncols;
+  bool whole;
+};
+
+// Length of the equal pieces, whole blocks, of kend keys in about ns of them.
+int piece_of(int kend, int ns) { return (int)ceil_div(ceil_div(kend, ns), kBlockKeys) * kBlockKeys; }
+
+struct PieceEstimate {
+  double us;      // of the launch
+  int64_t bytes;  // of the partial records and tickets, all kv heads
+};
+
+// Estimate of the chunk rows' launch with a tile in about nsplit(tile) pieces:
+// the greedy longest-first schedule of one kv head's pieces on its share of the
+// workgroup slots (two per CU), then the longest merge.  A piece costs 6.5 us and
+// its blocks (0.59 us each alone on a CU, 0.9 us beside another; D = 64 0.73 of
+// that) and, when it writes a partial record, 3.7 us per 128 x 128 outputs; the
+// records' bytes move at 2.87 TB/s.  Fitted on MI355X to 25 batches at 12 piece
+// lengths each, within 5% on the mean, when records were written with 8-byte
+// stores: a split launch now takes up to 7% less.  us < 0: too many items.
+template <class F>
+PieceEstimate estimate_pieces(const std::vector<ChunkTile>& tiles, F nsplit, int Hkv, int D, int ncu,
+                              std::vector<double>* cost, std::vector<double>* slot) {
   const int64_t slots = 2 * (int64_t)ncu;
   const double dim = D / 128.0, block_scale = D == 128 ? 1.0 : 0.733;
   int64_t pieces = 0;
-  for (int i = 0; i < n; ++i) {
-    if (q_len[i] <= 1) continue;
-    const int per = stays_whole(q_len[i], ctx_len[i], G, Hkv, ncu) ? 0 : keys;
-    pieces += ceil_div((int64_t)q_len[i] * G, kDefaultTileCols) *
-              chunk_nsplit(ctx_len[i] + q_len[i], per);
-    if (pieces * Hkv > 4 * slots) return -1.0;
+  for (const ChunkTile& t : tiles) {
+    pieces += nsplit(t);
+    if (pieces * Hkv > 4 * slots) return PieceEstimate{-1.0, 0};
   }
   const int64_t items = pieces * Hkv;
   const double fill = std::min(1.0, std::max(0.0, (double)(items - ncu) / ncu));
   const double block_us = (0.589 + (0.9 - 0.589) * fill) * block_scale;
+  PieceEstimate e{0.0, 0};
   double record_cols = 0;
   int max_split = 1;
   cost->clear();
-  for (int i = 0; i < n; ++i) {
-    const int c = q_len[i], u = ctx_len[i];
-    if (c <= 1) continue;
-    const int per = stays_whole(c, u, G, Hkv, ncu) ? 0 : keys;
-    const int64_t cols = (int64_t)c * G;
-    for (int64_t col0 = 0; col0 < cols; col0 += kDefaultTileCols) {
-      const int ncols = (int)std::min<int64_t>(kDefaultTileCols, cols - col0);
-      const int kend = u + (int)((col0 + ncols - 1) / G) + 1;
-      const int piece = (int)ceil_div(ceil_div(kend, chunk_nsplit(kend, per)), kBlockKeys) * kBlockKeys;
-      const int ns = (int)ceil_div(kend, piece);
-      max_split = std::max(max_split, ns);
-      if (ns > 1) record_cols += (double)ns * ncols;
-      for (int k0 = 0; k0 < kend; k0 += piece)
-        cost->push_back(6.48 + block_us * std::min(piece, kend - k0) / kBlockKeys +
-                        (ns > 1 ? 3.66 * ncols / 128.0 * dim : 0.0));
+  for (const ChunkTile& t : tiles) {
+    const int piece = piece_of(t.kend, nsplit(t)), ns = (int)ceil_div(t.kend, piece);
+    max_split = std::max(max_split, ns);
+    if (ns > 1) {
+      record_cols += (double)ns * t.ncols;
+      e.bytes += (ns * rec_floats(t.ncols, D) + 1) * 4 * Hkv;
     }
+    for (int k0 = 0; k0 < t.kend; k0 += piece)
+      cost->push_back(6.48 + block_us * std::min(piece, t.kend - k0) / kBlockKeys +
+                      (ns > 1 ? 3.66 * t.ncols / 128.0 * dim : 0.0));
   }
   std::sort(cost->begin(), cost->end(), std::greater<double>());
   slot->assign((size_t)std::max<int64_t>(1, slots / Hkv), 0.0);
-  double end = 0.0;
   for (double t : *cost) {
     std::pop_heap(slot->begin(), slot->end(), std::greater<double>());
     slot->back() += t;
-    end = std::max(end, slot->back());
+    e.us = std::max(e.us, slot->back());
     std::push_heap(slot->begin(), slot->end(), std::greater<double>());
   }
   if (max_split > 1)
-    end += 1.77 + 1.11 * max_split + record_cols * Hkv * D * 4.0 / 2.874e6;
-  return end + 6.96;
+    e.us += 1.77 + 1.11 * max_split + record_cols * Hkv * D * 4.0 / 2.874e6;
+  e.us += 6.96;
+  return e;
 }
 
 // The piece length (0: whole tiles) of a batch whose launch is its chunk rows;
-// -1 where the tiles are too many for the schedule to matter.  Longer pieces
-// first: shorter ones must win by 4%, and two in a row that estimate no better
-// end the search.
-int choose_piece_keys(const int32_t* q_len, const int32_t* ctx_len, int n, int G, int Hkv, int D,
-                      int ncu) {
+// -1 (the rule by half the makespan, whose piece count is usual(tile)) where the
+// tiles are too many for the schedule to matter.  Longer pieces first: shorter
+// ones must win by 4%, and two in a row that estimate no better end the search.
+// Their records fit the `scratch_left` bytes that the decode rows' records leave
+// of the library's scratch, or take no more than the usual rule's: a call that
+// runs in the scratch by that rule does by this one.
+template <class F>
+int choose_piece_keys(const std::vector<ChunkTile>& tiles, F usual, int64_t scratch_left, int Hkv,
+                      int D, int ncu) {
   std::vector<double> cost, slot;
   int longest = 0;
-  for (int i = 0; i < n; ++i)
-    if (q_len[i] > 1) longest = std::max(longest, ctx_len[i] + q_len[i]);
+  int64_t usual_bytes = 0;
+  for (const ChunkTile& t : tiles) {
+    longest = std::max(longest, t.kend);
+    const int ns = (int)ceil_div(t.kend, piece_of(t.kend, usual(t)));
+    if (ns > 1) usual_bytes += (ns * rec_floats(t.ncols, D) + 1) * 4 * Hkv;
+  }
+  const int64_t max_bytes = std::max(scratch_left, usual_bytes);
   struct Found {
     int keys;
     double us;
@@ -390,16 +406,19 @@ int choose_piece_keys(const int32_t* q_len, const int32_t* ctx_len, int n, int G
   int nf = 0, worse = 0;
   double best = 1e300;
   for (int k : {1, 2, 3, 4, 5, 6, 8, 11, 16}) {  // pieces of the longest tile (kMaxChunkSplits)
-    const int keys = k == 1 ? 0 : (int)ceil_div(ceil_div(longest, k), kBlockKeys) * kBlockKeys;
+    const int keys = k == 1 ? 0 : piece_of(longest, k);
     if (k > 1 && keys < kMinPieceKeys) break;
-    const double us = piece_estimate_us(q_len, ctx_len, n, G, Hkv, D, ncu, keys, &cost, &slot);
-    if (us < 0) {
+    const PieceEstimate e = estimate_pieces(
+        tiles, [&](const ChunkTile& t) { return chunk_nsplit(t.kend, t.whole ? 0 : keys); }, Hkv, D,
+        ncu, &cost, &slot);
+    if (e.us < 0) {
       if (keys == 0) return -1;
       break;
     }
-    found[nf++] = Found{keys, us};
-    worse = us < best ? 0 : worse + 1;
-    best = std::min(best, us);
+    if (e.bytes > max_bytes) break;
+    found[nf++] = Found{keys, e.us};
+    worse = e.us < best ? 0 : worse + 1;
+    best = std::min(best, e.us);
     if (worse == 2) break;
   }
   for (int k = 0; k < nf; ++k)
@@ -520,14 +539,6 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
     return (int32_t)p->groups.size() - 1;
   };
 
-  // Chunk batches without (much) decode work: the piece length with the
-  // shortest estimated launch, the longest one within 4% of it; 0: tiles whole.
-  const double decode_time = decode_blocks * kBlockKeys * D * 4.0 / kHbmRate;
-  int piece_keys = -1;  // -1: the rule by half the makespan below
-  if (tu.chunk_split_keys == 0 && tu.tile_cols == kDefaultTileCols && chunk_time_total > 0 &&
-      decode_time < kPiecesMaxDecodeShare * chunk_time_total / ncu)
-    piece_keys = choose_piece_keys(q_len, ctx_len, n, G, Hkv, D, ncu);
-
   // Key splits of a chunk tile (automatic): pieces of at most half the
   // estimated makespan, times `mult`, within [1, kMaxChunkSplits] and pieces of
   // at least kMinChunkSplitKeys keys.
@@ -545,7 +556,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
   // (decode items left out) is simulated for multipliers 1..3, each extra
   // piece charged kSplitCostKeys keys; a larger multiplier must win by 3%.
   int split_mult = 1;
-  if (tu.chunk_split_keys == 0 && piece_keys < 0 && makespan > 0) {
+  if (tu.chunk_split_keys == 0 && makespan > 0) {
     std::vector<double> best_pieces;
     double best = 0.0;
     for (int mult = 1; mult <= 3; ++mult) {
@@ -592,6 +603,38 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
     }
   }
 
+  // equal pieces of about dec_split keys per decode row (at least one), block aligned
+  auto decode_piece = [&](int keys) {
+    return piece_of(keys, std::max(1, (int)(((int64_t)keys + dec_split / 2) / dec_split)));
+  };
+
+  // Chunk batches without (much) decode work: the piece length with the
+  // shortest estimated launch, the longest one within 4% of it; 0: tiles whole.
+  const double decode_time = decode_blocks * kBlockKeys * D * 4.0 / kHbmRate;
+  int piece_keys = -1;  // -1: the rule by half the makespan above
+  if (tu.chunk_split_keys == 0 && tu.tile_cols == kDefaultTileCols && chunk_time_total > 0 &&
+      decode_time < kPiecesMaxDecodeShare * chunk_time_total / ncu) {
+    std::vector<ChunkTile> tiles;
+    int64_t scratch_left = kScratchBytes - 256 - kLaunchCounters * 4;
+    for (int i = 0; i < n; ++i) {
+      const int c = q_len[i], u = ctx_len[i];
+      if (c == 1) {
+        const int64_t ns = ceil_div((int64_t)u + 1, decode_piece(u + 1));
+        if (ns > 1) scratch_left -= (ns * rec_floats(G, D) + 1) * 4 * Hkv;
+      }
+      const int64_t total_cols = c > 1 ? (int64_t)c * G : 0;
+      for (int64_t col0 = 0; col0 < total_cols; col0 += kDefaultTileCols) {
+        if ((int64_t)tiles.size() * Hkv > 8 * ncu) break;  // more than the schedule is for
+        const int ncols = (int)std::min<int64_t>(kDefaultTileCols, total_cols - col0);
+        tiles.push_back(ChunkTile{u + (int)((col0 + ncols - 1) / G) + 1, ncols,
+                                  stays_whole(c, u, G, Hkv, ncu)});
+      }
+    }
+    piece_keys = choose_piece_keys(
+        tiles, [&](const ChunkTile& t) { return makespan > 0 ? auto_nsplit(t.kend, split_mult) : 1; },
+        scratch_left, Hkv, D, ncu);
+  }
+
   for (int i = 0; i < n; ++i) {
     const int c = q_len[i], u = ctx_len[i];
     if (c > 1) {
@@ -615,7 +658,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
             nsplit = chunk_nsplit(kend, stays_whole(c, u, G, Hkv, ncu) ? 0 : piece_keys);
           else if (makespan > 0)
             nsplit = auto_nsplit(kend, split_mult);
-          int piece = (int)ceil_div(ceil_div(kend, nsplit), kBlockKeys) * kBlockKeys;
+          const int piece = piece_of(kend, nsplit);
           nsplit = (int)ceil_div(kend, piece);
           const int32_t grp = nsplit > 1 ? add_group(nsplit, ncols) : -1;
           for (int sp = 0; sp < nsplit; ++sp) {
@@ -636,11 +679,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
         }
       }
     } else if (c == 1) {
-      const int keys = u + 1;
-      // round(keys / dec_split) equal pieces (at least one), block aligned
-      int nsplit = std::max(1, (int)(((int64_t)keys + dec_split / 2) / dec_split));
-      const int piece = (int)ceil_div(ceil_div(keys, nsplit), kBlockKeys) * kBlockKeys;
-      nsplit = (int)ceil_div(keys, piece);
+      const int keys = u + 1, piece = decode_piece(keys), nsplit = (int)ceil_div(keys, piece);
       if ((int64_t)raw.size() + (int64_t)nsplit * Hkv > kMaxItems) return SSA_ERR_LENGTH;
       for (int h = 0; h < Hkv; ++h) {
         const int32_t grp = nsplit > 1 ? add_group(nsplit, G) : -1;

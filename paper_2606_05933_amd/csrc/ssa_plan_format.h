@@ -29,6 +29,8 @@ constexpr int kLaunchCounters = 4;  // workspace words ahead of the merge ticket
 constexpr int kWsStatusWord = 2;    // the status word among them (ssa.h)
 constexpr int kWsDispatched = 3;    // set once a chunk launch has started all its workgroups
 constexpr int kDefaultWaitPolls = 1 << 21;
+// Scratch of ssa_append_attention_static, which refuses plans that need more.
+constexpr int64_t kScratchBytes = (int64_t)32 << 20;
 
 // Float offset of o in a partial record of ncols columns, and the record's size.
 constexpr int64_t rec_o_off(int ncols) { return ((int64_t)2 * ncols + 3) / 4 * 4; }

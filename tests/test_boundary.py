@@ -284,6 +284,19 @@ def test_chunk_pieces_without_decode_rows(hq, hkv, q, ctx, items):
             assert len(t) == 1 or (t["key1"] - t["key0"])[:-1].min() >= 512
 
 
+@pytest.mark.parametrize("hq,hkv,q,ctx", [
+    (28, 4, [3220], [6491]), (28, 4, [2074, 109, 5], [10667, 19590, 5666]),
+    (8, 1, [570, 1732, 169, 102, 1815, 3364, 5, 1760],
+     [1333, 7817, 62529, 1833, 5163, 7834, 74, 58]),
+    (32, 8, [1034, 50, 2553, 17, 1, 1], [21550, 7, 5629, 55707, 257, 2355])])
+def test_chunk_pieces_fit_the_scratch(hq, hkv, q, ctx):
+    """ssa_append_attention_static takes plans of at most 32 MiB.  By the rule for
+    batches with more decode work these need 0 to 24 MiB: the pieces chosen for
+    chunk rows alone must not take them past the limit."""
+    shape = shape_of(hq, hkv, 128, np.array(q, np.int32), np.array(ctx, np.int32))
+    assert ssa.ssa_plan_size(shape, q, ctx)[1] <= 32 << 20
+
+
 def test_plan_is_deterministic():
     q_len = np.array([300, 1, 1, 1], np.int32)
     ctx_len = np.array([0, 5, 900, 40], np.int32)
