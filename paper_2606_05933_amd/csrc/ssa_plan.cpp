@@ -304,9 +304,10 @@ void order_items(const std::vector<WorkItem>& items, const std::vector<double>& 
 }
 
 // Pieces of a tile of kend keys cut at about `keys` keys (0: whole): equal
-// pieces, whole blocks.
+// pieces, whole blocks, each of at least kMinPieceKeys keys but for the last one's
+// rounding, however much shorter than the batch's longest tile this one is.
 int chunk_nsplit(int kend, int keys) {
-  return keys <= 0 ? 1 : (int)ceil_div(kend, keys);
+  return keys <= 0 ? 1 : std::max(1, std::min((int)ceil_div(kend, keys), kend / kMinPieceKeys));
 }
 // A chunk most of whose keys are its own new rows, with tiles for half of the
 // workgroup slots or more, stays whole: every piece of it would wait for the

@@ -268,20 +268,39 @@ def test_automatic_chunk_splits_fill_the_last_round():
     (64, 8, [1024], [8192], 512),           # one round of whole tiles
     (32, 8, [2048], [0], 512),              # its keys are its own new rows: whole
     (32, 8, [100], [300], 32),              # too short to cut
-    (8, 1, [100], [20000], 112)])           # 7 tiles in 16 pieces
+    (8, 1, [100], [20000], 112),            # 7 tiles in 16 pieces
+    # several requests: the shorter ones are not cut below 512 keys
+    (28, 4, [9, 64], [4000, 700], None), (32, 8, [100, 100], [3000, 800], None),
+    (8, 1, [93, 547, 97], [16, 54, 2750], None), (8, 8, [60, 9, 200], [9000, 1030, 1100], None)])
 def test_chunk_pieces_without_decode_rows(hq, hkv, q, ctx, items):
     """Pieces cover each tile's keys, in whole blocks, at least 512 keys long but
-    for the last one; a mostly decoding batch keeps the rule by its makespan."""
+    for the last one."""
     shape = shape_of(hq, hkv, 128, np.array(q, np.int32), np.array(ctx, np.int32))
     blob, info = ssa.ssa_plan(shape, q, ctx)
-    assert info.num_chunk_items == items
+    assert items in (None, info.num_chunk_items)
     it = parse(blob)[2]
-    for col0 in np.unique(it["col0"]):
-        for h in range(hkv):
-            t = np.sort(it[(it["col0"] == col0) & (it["kvh"] == h)], order="key0")
-            assert t["key0"][0] == 0 and np.array_equal(t["key0"][1:], t["key1"][:-1])
-            assert (t["key0"] % 32 == 0).all()
-            assert len(t) == 1 or (t["key1"] - t["key0"])[:-1].min() >= 512
+    for req, col0, h in {(int(i["req"]), int(i["col0"]), int(i["kvh"])) for i in it}:
+        t = np.sort(it[(it["req"] == req) & (it["col0"] == col0) & (it["kvh"] == h)], order="key0")
+        assert t["key0"][0] == 0 and np.array_equal(t["key0"][1:], t["key1"][:-1])
+        assert (t["key0"] % 32 == 0).all()
+        assert len(t) == 1 or (t["key1"] - t["key0"])[:-1].min() >= 512
+
+
+def test_chunk_pieces_beside_decode_rows_keep_the_rule_by_the_makespan():
+    """A batch whose decode rows take a tenth or more of the chunk rows' time: tiles
+    are cut by the makespan, into pieces of 1024 keys or more."""
+    q, ctx = [250] + [1] * 8, [3001] + [8000] * 8
+    blob, info = ssa.ssa_plan(shape_of(32, 8, 128, np.array(q, np.int32), np.array(ctx, np.int32)),
+                              q, ctx)
+    # a tile takes 41 us by the nominal rates, over half of the makespan of 58 us
+    # and under the whole of it: two pieces (four without the decode rows)
+    assert info.num_chunk_items == 128
+    q, ctx = [64] + [1] * 2, [16000] + [2000] * 2
+    blob, info = ssa.ssa_plan(shape_of(32, 8, 128, np.array(q, np.int32), np.array(ctx, np.int32)),
+                              q, ctx)
+    it = parse(blob)[2]
+    it = it[it["kind"] == 0]
+    assert len(it) > 16 and (it["key1"] - it["key0"])[it["key1"] < 16000].min() >= 1024
 
 
 @pytest.mark.parametrize("hq,hkv,q,ctx", [
