@@ -42,12 +42,19 @@ constexpr double kSplitCostKeys = 768.0;
 // 3001 cached, 32/8 heads: 43 us in pieces of 832, 49 us of 672; 39 us in pieces
 // of 832 since the records are written with 16-byte stores).
 constexpr int kMinPieceKeys = 512;
-// Batches whose decode rows (at kHbmRate) take under this share of the chunk
-// rows' estimated time: the chunk pieces are chosen by piece_estimate_us.  With
-// more decode work beside them the pieces' records and slots cost the decode
-// items, and the rule by half the makespan measured within 3% of the best fixed
-// length on ten mixed batches.
+// The chunk pieces are chosen by estimate_pieces for batches whose decode rows (at
+// kHbmRate) take under kPiecesMaxDecodeShare of the chunk rows' estimated time,
+// and where the keys appended in the launch (for a chunk with more new rows than
+// cached ones, all its keys) are at most kPiecesMaxOwnShare of the chunk rows'
+// key visits: the estimate describes neither the decode items nor the waits for
+// appended rows.  A cut has to be estimated under kPiecesMaxCost of the makespan
+// rule's time: nine tenths of the estimates are within 10%, and the ratio of two
+// of them is nearer.  Of 3000 drawn batches about 350 are cut by it, in 0.80 of
+// the makespan rule's time on the geometric mean and 1.02 at worst; at an own
+// share of 0.2, three took 1.04 to 1.24.
 constexpr double kPiecesMaxDecodeShare = 0.1;
+constexpr double kPiecesMaxOwnShare = 0.08;
+constexpr double kPiecesMaxCost = 0.86;
 // Decode key ranges are cut into equal pieces of about this many keys: long
 // enough that the load latency at the start of an item is amortised over 32
 // blocks per wave, short enough that long and short contexts balance over the
@@ -309,15 +316,9 @@ void order_items(const std::vector<WorkItem>& items, const std::vector<double>& 
 int chunk_nsplit(int kend, int keys) {
   return keys <= 0 ? 1 : std::max(1, std::min((int)ceil_div(kend, keys), kend / kMinPieceKeys));
 }
-// A chunk most of whose keys are its own new rows, with tiles for half of the
-// workgroup slots or more, stays whole: every piece of it would wait for the
-// rows appended in the same launch (2048 tokens on an empty cache, 32/8 heads:
-// 74 us whole, 82 us in pieces of 1536).
-bool stays_whole(int c, int u, int G, int Hkv, int ncu) {
-  return u < c / 2 && ceil_div((int64_t)c * G, kDefaultTileCols) * Hkv >= ncu;
-}
-
-// A chunk tile of one kv head; `whole`: its chunk stays whole (stays_whole).
+// A chunk tile of one kv head; `whole`: most of its chunk's keys are its own new
+// rows, and every piece of it would wait for the rows appended in the same launch
+// (2048 tokens on an empty cache, 32/8 heads: 74 us whole, 82 us in pieces of 1536).
 struct ChunkTile {
   int kend, ncols;
   bool whole;
@@ -333,39 +334,38 @@ struct PieceEstimate {
 
 // Estimate of the chunk rows' launch with a tile in about nsplit(tile) pieces:
 // the greedy longest-first schedule of one kv head's pieces on its share of the
-// workgroup slots (two per CU), then the longest merge.  A piece costs 6.5 us and
-// its blocks (0.59 us each alone on a CU, 0.9 us beside another; D = 64 0.73 of
-// that) and, when it writes a partial record, 3.7 us per 128 x 128 outputs; the
-// records' bytes move at 2.87 TB/s.  Fitted on MI355X to 25 batches at 12 piece
-// lengths each, within 5% on the mean, when records were written with 8-byte
-// stores: a split launch now takes up to 7% less.  us < 0: too many items.
+// `slots` workgroup slots, then the longest merge.  A piece costs 8.8 us and
+// its blocks (0.59 us each alone on its CU; beside another more, up to 0.79 us on
+// a full chip, steeply at first: a few CUs that hold two workgroups already set
+// the pace of the longest pieces; D = 64 0.76 of that) and, when it writes a
+// partial record, 3.4 us per 128 x 128 outputs; a merge costs by its rounds of
+// loads (merge_lds); the records' bytes move at 4.9 TB/s.  Fitted on MI355X to 317
+// batches whose chunks lie mostly on cached rows, each under two plans and up to
+// nine piece lengths: half of the estimates within 3.4%, nine tenths within 10%.
 template <class F>
 PieceEstimate estimate_pieces(const std::vector<ChunkTile>& tiles, F nsplit, int Hkv, int D, int ncu,
-                              std::vector<double>* cost, std::vector<double>* slot) {
-  const int64_t slots = 2 * (int64_t)ncu;
-  const double dim = D / 128.0, block_scale = D == 128 ? 1.0 : 0.733;
-  int64_t pieces = 0;
-  for (const ChunkTile& t : tiles) {
-    pieces += nsplit(t);
-    if (pieces * Hkv > 4 * slots) return PieceEstimate{-1.0, 0};
-  }
-  const int64_t items = pieces * Hkv;
+                              int64_t slots, std::vector<double>* cost, std::vector<double>* slot) {
+  const double dim = D / 128.0, block_scale = D == 128 ? 1.0 : 0.762;
+  int64_t items = 0;
+  for (const ChunkTile& t : tiles) items += (int64_t)nsplit(t) * Hkv;
   const double fill = std::min(1.0, std::max(0.0, (double)(items - ncu) / ncu));
-  const double block_us = (0.589 + (0.9 - 0.589) * fill) * block_scale;
+  const double block_us = (0.587 + 0.2 * std::pow(fill, 0.29)) * block_scale;
   PieceEstimate e{0.0, 0};
-  double record_cols = 0;
-  int max_split = 1;
+  double record_cols = 0, merge = 0;
   cost->clear();
   for (const ChunkTile& t : tiles) {
     const int piece = piece_of(t.kend, nsplit(t)), ns = (int)ceil_div(t.kend, piece);
-    max_split = std::max(max_split, ns);
     if (ns > 1) {
       record_cols += (double)ns * t.ncols;
       e.bytes += (ns * rec_floats(t.ncols, D) + 1) * 4 * Hkv;
+      const int units = t.ncols * D / 4;
+      const int64_t rounds = units > 512 ? ceil_div(units, 1024) * ceil_div(ns, 4)
+                                         : ceil_div(units, 512) * ceil_div(ns, 8);
+      merge = std::max(merge, 1.52 + 1.17 * rounds + 0.166 * ns);
     }
     for (int k0 = 0; k0 < t.kend; k0 += piece)
-      cost->push_back(6.48 + block_us * std::min(piece, t.kend - k0) / kBlockKeys +
-                      (ns > 1 ? 3.66 * t.ncols / 128.0 * dim : 0.0));
+      cost->push_back(8.79 + block_us * ceil_div(std::min(piece, t.kend - k0), kBlockKeys) +
+                      (ns > 1 ? 3.4 * t.ncols / 128.0 * dim : 0.0));
   }
   std::sort(cost->begin(), cost->end(), std::greater<double>());
   slot->assign((size_t)std::max<int64_t>(1, slots / Hkv), 0.0);
@@ -375,56 +375,42 @@ PieceEstimate estimate_pieces(const std::vector<ChunkTile>& tiles, F nsplit, int
     e.us = std::max(e.us, slot->back());
     std::push_heap(slot->begin(), slot->end(), std::greater<double>());
   }
-  if (max_split > 1)
-    e.us += 1.77 + 1.11 * max_split + record_cols * Hkv * D * 4.0 / 2.874e6;
-  e.us += 6.96;
+  e.us += merge + record_cols * Hkv * D * 4.0 / 4.88e6 + 2.55;
   return e;
 }
 
 // The piece length (0: whole tiles) of a batch whose launch is its chunk rows;
-// -1 (the rule by half the makespan, whose piece count is usual(tile)) where the
-// tiles are too many for the schedule to matter.  Longer pieces first: shorter
-// ones must win by 4%, and two in a row that estimate no better end the search.
+// -1, the rule by half the makespan, whose piece count is usual(tile), unless a
+// length is estimated to take under kPiecesMaxCost of that rule's time.  Longer
+// pieces first: two lengths in a row that estimate no better end the search.
 // Their records fit the `scratch_left` bytes that the decode rows' records leave
 // of the library's scratch, or take no more than the usual rule's: a call that
-// runs in the scratch by that rule does by this one.
+// runs in the scratch by that rule does by this one.  slots: the workgroup slots
+// (two per CU) that the decode items leave.
 template <class F>
-int choose_piece_keys(const std::vector<ChunkTile>& tiles, F usual, int64_t scratch_left, int Hkv,
-                      int D, int ncu) {
+int choose_piece_keys(const std::vector<ChunkTile>& tiles, F usual, int64_t scratch_left,
+                      int64_t slots, int Hkv, int D, int ncu) {
   std::vector<double> cost, slot;
   int longest = 0;
-  int64_t usual_bytes = 0;
-  for (const ChunkTile& t : tiles) {
-    longest = std::max(longest, t.kend);
-    const int ns = (int)ceil_div(t.kend, piece_of(t.kend, usual(t)));
-    if (ns > 1) usual_bytes += (ns * rec_floats(t.ncols, D) + 1) * 4 * Hkv;
-  }
-  const int64_t max_bytes = std::max(scratch_left, usual_bytes);
-  struct Found {
-    int keys;
-    double us;
-  } found[9];
-  int nf = 0, worse = 0;
-  double best = 1e300;
+  for (const ChunkTile& t : tiles) longest = std::max(longest, t.kend);
+  const PieceEstimate by_makespan = estimate_pieces(tiles, usual, Hkv, D, ncu, slots, &cost, &slot);
+  const int64_t max_bytes = std::max(scratch_left, by_makespan.bytes);
+  double best = kPiecesMaxCost * by_makespan.us;
+  double lowest = 1e300;
+  int best_keys = -1, worse = 0;
   for (int k : {1, 2, 3, 4, 5, 6, 8, 11, 16}) {  // pieces of the longest tile (kMaxChunkSplits)
     const int keys = k == 1 ? 0 : piece_of(longest, k);
     if (k > 1 && keys < kMinPieceKeys) break;
     const PieceEstimate e = estimate_pieces(
         tiles, [&](const ChunkTile& t) { return chunk_nsplit(t.kend, t.whole ? 0 : keys); }, Hkv, D,
-        ncu, &cost, &slot);
-    if (e.us < 0) {
-      if (keys == 0) return -1;
-      break;
-    }
+        ncu, slots, &cost, &slot);
     if (e.bytes > max_bytes) break;
-    found[nf++] = Found{keys, e.us};
-    worse = e.us < best ? 0 : worse + 1;
-    best = std::min(best, e.us);
+    worse = e.us < lowest ? 0 : worse + 1;
+    lowest = std::min(lowest, e.us);
+    if (e.us < best) best = e.us, best_keys = keys;
     if (worse == 2) break;
   }
-  for (int k = 0; k < nf; ++k)
-    if (found[k].us <= 1.04 * best) return found[k].keys;
-  return 0;
+  return best_keys;
 }
 
 int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int32_t n,
@@ -609,31 +595,42 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
     return piece_of(keys, std::max(1, (int)(((int64_t)keys + dec_split / 2) / dec_split)));
   };
 
-  // Chunk batches without (much) decode work: the piece length with the
-  // shortest estimated launch, the longest one within 4% of it; 0: tiles whole.
+  // Chunk batches without (much) decode work, on cached rows: the piece length with
+  // the shortest estimated launch, if it is well under the makespan rule's.
   const double decode_time = decode_blocks * kBlockKeys * D * 4.0 / kHbmRate;
+  double work = 0, own_work = 0;
+  int64_t num_tiles = 0;
+  for (int i = 0; i < n; ++i)
+    if (q_len[i] > 1) {
+      const double w = (double)q_len[i] * (ctx_len[i] + 0.5 * q_len[i]);
+      work += w;
+      own_work += ctx_len[i] < q_len[i] ? w : 0.5 * q_len[i] * (double)q_len[i];
+      num_tiles += ceil_div((int64_t)q_len[i] * G, kDefaultTileCols);
+    }
   int piece_keys = -1;  // -1: the rule by half the makespan above
-  if (tu.chunk_split_keys == 0 && tu.tile_cols == kDefaultTileCols && chunk_time_total > 0 &&
+  // (beyond four rounds of the slots the last round's loss is small)
+  if (tu.chunk_split_keys == 0 && tu.tile_cols == kDefaultTileCols && makespan > 0 && work > 0 &&
+      own_work <= kPiecesMaxOwnShare * work && num_tiles * Hkv <= 8 * (int64_t)ncu &&
       decode_time < kPiecesMaxDecodeShare * chunk_time_total / ncu) {
     std::vector<ChunkTile> tiles;
-    int64_t scratch_left = kScratchBytes - 256 - kLaunchCounters * 4;
+    tiles.reserve((size_t)num_tiles);
+    int64_t scratch_left = kScratchBytes - 256 - kLaunchCounters * 4, decode_items = 0;
     for (int i = 0; i < n; ++i) {
       const int c = q_len[i], u = ctx_len[i];
       if (c == 1) {
         const int64_t ns = ceil_div((int64_t)u + 1, decode_piece(u + 1));
         if (ns > 1) scratch_left -= (ns * rec_floats(G, D) + 1) * 4 * Hkv;
+        decode_items += ns * Hkv;
       }
       const int64_t total_cols = c > 1 ? (int64_t)c * G : 0;
       for (int64_t col0 = 0; col0 < total_cols; col0 += kDefaultTileCols) {
-        if ((int64_t)tiles.size() * Hkv > 8 * ncu) break;  // more than the schedule is for
         const int ncols = (int)std::min<int64_t>(kDefaultTileCols, total_cols - col0);
-        tiles.push_back(ChunkTile{u + (int)((col0 + ncols - 1) / G) + 1, ncols,
-                                  stays_whole(c, u, G, Hkv, ncu)});
+        tiles.push_back(ChunkTile{u + (int)((col0 + ncols - 1) / G) + 1, ncols, u < c});
       }
     }
     piece_keys = choose_piece_keys(
-        tiles, [&](const ChunkTile& t) { return makespan > 0 ? auto_nsplit(t.kend, split_mult) : 1; },
-        scratch_left, Hkv, D, ncu);
+        tiles, [&](const ChunkTile& t) { return auto_nsplit(t.kend, split_mult); }, scratch_left,
+        std::max<int64_t>(ncu, 2 * (int64_t)ncu - decode_items), Hkv, D, ncu);
   }
 
   for (int i = 0; i < n; ++i) {
@@ -656,7 +653,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
           if (tu.chunk_split_keys > 0)
             nsplit = (int)ceil_div(kend, tu.chunk_split_keys);
           else if (piece_keys >= 0)
-            nsplit = chunk_nsplit(kend, stays_whole(c, u, G, Hkv, ncu) ? 0 : piece_keys);
+            nsplit = chunk_nsplit(kend, u < c ? 0 : piece_keys);
           else if (makespan > 0)
             nsplit = auto_nsplit(kend, split_mult);
           const int piece = piece_of(kend, nsplit);
@@ -719,7 +716,9 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
   //
   // mix_order 5 (for ssa_append_attention_streams): where the two-stream split
   // pays, all chunk items first and the split recorded in the plan; otherwise
-  // the automatic order and one launch.
+  // the automatic order and one launch.  With pieces by estimate_pieces there is
+  // little decode work, and one launch is faster (686 tokens on 32239 cached
+  // beside five decodes, 8/1 heads: 118 us, 154 on two streams).
   size_t nchunk = 0;
   double decode_kv_bytes = 0;
   for (const WorkItem& it : raw) {
@@ -728,7 +727,7 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
   }
   const double beside_budget = in.chunk_flops / kBesideChunkFlops * kBesideDecodeBytes;
   const bool split = tu.streams == 2 ||
-                     (tu.streams == 1 && D == 128 && Hq / Hkv <= 8 &&
+                     (tu.streams == 1 && piece_keys < 0 && D == 128 && Hq / Hkv <= 8 &&
                       nchunk >= kBesideMinFill * tu.num_cus && nchunk <= 2 * (size_t)tu.num_cus &&
                       decode_kv_bytes > 0 &&
                       beside_budget >= kBesideMinCover * decode_kv_bytes);

@@ -269,6 +269,7 @@ def test_automatic_chunk_splits_fill_the_last_round():
     (32, 8, [2048], [0], 512),              # its keys are its own new rows: whole
     (32, 8, [100], [300], 32),              # too short to cut
     (8, 1, [100], [20000], 112),            # 7 tiles in 16 pieces
+    (64, 8, [600], [20000], 1824),          # 304 tiles, between one and two per CU: not whole
     # several requests: the shorter ones are not cut below 512 keys
     (28, 4, [9, 64], [4000, 700], None), (32, 8, [100, 100], [3000, 800], None),
     (8, 1, [93, 547, 97], [16, 54, 2750], None), (8, 8, [60, 9, 200], [9000, 1030, 1100], None)])
