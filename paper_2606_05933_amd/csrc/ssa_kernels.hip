@@ -519,18 +519,28 @@ __device__ void merge_lds(const AttnArgs& a, const WorkItem& it, const ReqEntry&
   }
 }
 
-template <int D>
+// CHUNK: the records of a chunk tile; otherwise of a decode row's G <= 16 columns,
+// at most two units per thread, so that each kind of item holds only the passes
+// its sizes take (with all of them behind both, the compiler calls instead of
+// inlining them, and the fused kernel takes 248 registers and scratch memory).
+template <int D, bool CHUNK>
 __device__ void merge_group(const AttnArgs& a, const WorkItem& it, const ReqEntry& rq,
                             const MergeGroup& grp, char* lds) {
   const RecordReader rd(reinterpret_cast<const float*>(a.ws + a.ws_partials_off) + grp.ws_off);
   const int C = grp.ncols, S = grp.nsplit;
   const int units = C * (D / 4);
   static_assert((kLdsMergeSplits + 1) * 128 * 4 <= Cfg<D>::LDS - 16, "weights fit the staging area");
+  static_assert(16 * (D / 4) <= 2 * kThreads, "units of a decode row");
   if (S <= kLdsMergeSplits) {
-    if (units > 2 * kThreads) merge_lds<D, 4, 4>(a, it, rq, rd, C, S, lds);
+    if (CHUNK && units > 2 * kThreads) merge_lds<D, 4, 4>(a, it, rq, rd, C, S, lds);
     else merge_lds<D, 2, 8>(a, it, rq, rd, C, S, lds);
+  } else if (CHUNK && units >= 4 * kThreads) {
+    // short pieces asked for: any number of splits, many units, of which four per
+    // thread share a round of loads (64 rows on 16000 cached, 32/8 heads, in 21
+    // pieces: 119 us, 138 with one unit and 8 splits per round)
+    for (int u0 = 0; u0 < units; u0 += 4 * kThreads) merge_pass<D, 4, 4, 2>(a, it, rq, rd, C, S, u0);
   } else {
-    // very long contexts, or short pieces asked for: any number of splits
+    // decode rows on very long contexts, narrow chunk tiles in short pieces
     for (int u0 = 0; u0 < units; u0 += kThreads) merge_pass<D, 1, 8, 8>(a, it, rq, rd, C, S, u0);
   }
 }
@@ -546,7 +556,7 @@ __device__ __forceinline__ MergeGroup item_group(const AttnArgs& a, const WorkIt
 // After this workgroup wrote its partial record (device-scope stores): wait for
 // the stores, take a ticket; the last of the group's items merges and resets
 // the ticket for the next launch.
-template <int D>
+template <int D, bool CHUNK>
 __device__ void finish_split(const AttnArgs& a, const WorkItem& it, const ReqEntry& rq,
                              const MergeGroup& grp, char* lds) {
   // the last word of the kernel's LDS buffer: past the decode merge area, and
@@ -563,7 +573,7 @@ __device__ void finish_split(const AttnArgs& a, const WorkItem& it, const ReqEnt
   }
   __syncthreads();
   if (!s_last) return;
-  merge_group<D>(a, it, rq, grp, lds);
+  merge_group<D, CHUNK>(a, it, rq, grp, lds);
   if (threadIdx.x == 0)
     __hip_atomic_store(&tickets[it.group], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1024,7 +1034,7 @@ __device__ void chunk_item(const AttnArgs& a, const WorkItem& it, const ReqEntry
       for (int mt = 0; mt < MT; ++mt)  // 16-byte aligned, as records and o rows are
         wr(at + mt * 64, __builtin_bit_cast(u32x4, o[nt][mt]));
     }
-    finish_split<D>(a, it, rq, grp, lds);
+    finish_split<D, true>(a, it, rq, grp, lds);
   }
 }
 
@@ -1231,7 +1241,7 @@ __device__ void decode_item(const AttnArgs& a, const WorkItem& it, const ReqEntr
                    acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
     }
   }
-  if (rec) finish_split<D>(a, it, rq, grp, lds);
+  if (rec) finish_split<D, false>(a, it, rq, grp, lds);
 }
 
 // One attention work item of the plan.

@@ -492,11 +492,13 @@ def test_fused_wait_time_out_is_reported_and_every_workgroup_exits(torch_dev):
 
 @pytest.mark.parametrize("hq,hkv,d,tile,splits", [
     (8, 2, 128, 128, 2), (8, 2, 128, 128, 5), (8, 1, 128, 128, 16), (8, 1, 128, 128, 17),
-    (28, 4, 128, 64, 4), (8, 8, 64, 128, 15), (8, 8, 64, 32, 17)])
+    (28, 4, 128, 64, 4), (8, 8, 64, 128, 15), (8, 8, 64, 32, 17), (8, 1, 64, 128, 19),
+    (8, 1, 128, 128, 33), (16, 1, 128, 128, 18)])
 def test_merges_of_many_splits(torch_dev, hq, hkv, d, tile, splits):
     """Chunk tiles and decode rows cut in so many pieces: rounds of four or eight
     splits with remainders, and either side of the 16 splits whose weights one
-    pass holds; full and narrow last tiles."""
+    pass holds; full and narrow last tiles, past 16 splits both the wide tiles'
+    passes and the narrow ones'."""
     from paper_2606_05933_amd import ssa, workload
     u = 32 * splits - 60
     c = 37 if hq // hkv < 8 else 18
