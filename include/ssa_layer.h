@@ -88,6 +88,18 @@ int ssa_linear(int32_t m, int32_t n, int32_t k, int32_t epilogue, const uint16_t
                size_t ws_bytes, void* stream);
 
 /*
+ * How ssa_linear runs a product: workgroups of `threads` threads, each a tile of
+ * tile_m tokens by tile_n outputs over one of `splits` ranges of K, in a grid of
+ * tiles_m x tiles_n x splits (all zero for M == 0).  Errors: SSA_ERR_ARG,
+ * SSA_ERR_NULL.
+ */
+typedef struct ssa_linear_plan_info {
+  int32_t tile_m, tile_n, threads;
+  int32_t tiles_m, tiles_n, splits;
+} ssa_linear_plan_info;
+int ssa_linear_plan(int32_t m, int32_t n, int32_t k, ssa_linear_plan_info* info);
+
+/*
  * RMSNorm of each row: out = x / sqrt(mean(x^2) + eps) * weight, in fp32, one
  * bf16 rounding.  x, out [M, N] bf16 (distinct buffers); weight [N] bf16.
  * Requires N % 8 == 0, N <= 8192, eps >= 0.

@@ -441,11 +441,11 @@ enum {
 };
 
 struct CfgShape {
-  int bm, bn, occ, stages;
+  int bm, bn, occ, stages, threads;
 };
 template <class C>
 constexpr CfgShape shape_of() {
-  return CfgShape{C::BM, C::BN, C::OCC, C::STAGES};
+  return CfgShape{C::BM, C::BN, C::OCC, C::STAGES, C::kThreads};
 }
 constexpr CfgShape kCfgShapes[kNumCfgs] = {
     shape_of<Cfg32x64>(),   shape_of<Cfg64x64>(),   shape_of<Cfg64x128>(),    shape_of<Cfg96x64>(),
@@ -516,16 +516,25 @@ double plan_cost(const GemmPlan& c, int m, int n, int k) {
   return t;
 }
 
+// A launch holds fewer than 2^32 threads.
+bool launchable(const GemmPlan& c) {
+  return (int64_t)c.tiles_m * c.tiles_n * c.splits * kCfgShapes[c.cfg].threads < INT64_C(1) << 32;
+}
+
 // The cheapest plan by plan_cost over the configurations and 1 .. 12 splits of
 // at least 3 K blocks that leave at most 1100 workgroups.
 GemmPlan choose_plan(int m, int n, int k) {
   if (k >= kWideK) return make_plan(kCfg32x64, m, n, k, 1);
   GemmPlan best{};
   double best_cost = 1e300;
+  const bool small_fits = launchable(make_plan(kCfg32x64, m, n, k, 1));
   for (int cfg = 0; cfg < kNumCfgs; ++cfg) {
     const CfgShape& cs = kCfgShapes[cfg];
     // half-empty tiles, and tiles far smaller than a long batch, never win
-    if (n % cs.bn || (cs.bm > 32 && cs.bm >= 2 * m) || (cs.bm < 96 && m >= 1024)) continue;
+    if (n % cs.bn || (small_fits && cs.bm > 32 && cs.bm >= 2 * m) || (cs.bm < 96 && m >= 1024))
+      continue;
+    // (every size that check_linear takes is launchable in 64 x 128 tiles)
+    if (!launchable(make_plan(cfg, m, n, k, 1))) continue;
     for (int s : {1, 2, 3, 4, 5, 6, 8, 12}) {
       const GemmPlan c = make_plan(cfg, m, n, k, s);
       if (s > 1 && ((int64_t)c.tiles_m * c.tiles_n * s > 1100 || c.kblocks / s < 3)) break;
@@ -584,9 +593,9 @@ int launch_linear(const GemmPlan& c, int m, int n, int k, int epilogue, const ui
   return hipGetLastError() == hipSuccess ? SSA_OK : SSA_ERR_HIP;
 }
 
-// Sizes whose tile and workgroup counts fit the plan's 32-bit fields (at most
-// 2^24 tiles of the smallest tile, 32 x 128, each split at most kblocks / 4
-// ways) and whose operands stay below 2^40 elements.
+// Sizes whose tile counts fit the plan's 32-bit fields (at most 2^25 of the
+// smallest tile, 32 x 64; only up to 512 tiles are split), which some
+// configuration's grid can hold, and whose operands stay below 2^40 elements.
 int check_linear(int32_t m, int32_t n, int32_t k, int32_t epilogue) {
   if (m < 0 || n <= 0 || k <= 0 || n % 128 || k % BK) return SSA_ERR_ARG;
   if (epilogue < SSA_EPILOGUE_NONE || epilogue > SSA_EPILOGUE_SWIGLU) return SSA_ERR_ARG;
@@ -620,6 +629,18 @@ int ssa_linear_workspace_size(int32_t m, int32_t n, int32_t k, size_t* ws_bytes)
   const int rc = check_linear(m, n, k, SSA_EPILOGUE_NONE);
   if (rc) return rc;
   *ws_bytes = m == 0 ? 0 : choose_plan(m, n, k).ws;
+  return SSA_OK;
+}
+
+int ssa_linear_plan(int32_t m, int32_t n, int32_t k, ssa_linear_plan_info* info) {
+  if (!info) return SSA_ERR_NULL;
+  const int rc = check_linear(m, n, k, SSA_EPILOGUE_NONE);
+  if (rc) return rc;
+  *info = ssa_linear_plan_info{};
+  if (m == 0) return SSA_OK;
+  const GemmPlan c = choose_plan(m, n, k);
+  const CfgShape& cs = kCfgShapes[c.cfg];
+  *info = ssa_linear_plan_info{cs.bm, cs.bn, cs.threads, c.tiles_m, c.tiles_n, c.splits};
   return SSA_OK;
 }
 

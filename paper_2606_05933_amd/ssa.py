@@ -87,6 +87,11 @@ class SsaLayerWeights(ctypes.Structure):
                 ("eps", ctypes.c_float)]
 
 
+class SsaLinearPlanInfo(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("tile_m", "tile_n", "threads", "tiles_m", "tiles_n",
+                                              "splits")]
+
+
 class SsaPlanInfo(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int32) for n in (
         "num_reqs", "num_tokens", "num_decode_reqs", "num_chunk_reqs", "num_items",
@@ -176,6 +181,7 @@ def _load():
     lib.ssa_rope_append.argtypes = [P(SsaShape), vp, vp, vp, vp, i32, vp, vp, vp, vp, vp]
     lib.ssa_rope_append.restype = ctypes.c_int
     lib.ssa_linear_workspace_size.argtypes = [i32, i32, i32, P(sz)]
+    lib.ssa_linear_plan.argtypes = [i32, i32, i32, P(SsaLinearPlanInfo)]
     lib.ssa_linear.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp, vp, sz, vp]
     lib.ssa_rms_norm.argtypes = [i32, i32, vp, vp, ctypes.c_float, vp, vp]
     lib.ssa_check_block_table.argtypes = [P(SsaShape), vp, vp]
@@ -208,7 +214,8 @@ EXPORTED = ("ssa_status_string", "ssa_plan_size", "ssa_plan", "ssa_check_block_t
             "ssa_predictor_add",
             "ssa_predictor_fit", "ssa_predictor_predict", "ssa_form_batch", "ssa_time_to_budget",
             "ssa_sliding_chunker", "ssa_priority_sort", "ssa_batch_constructor",
-            "ssa_rope_append", "ssa_rope_table", "ssa_linear_workspace_size", "ssa_linear", "ssa_rms_norm",
+            "ssa_rope_append", "ssa_rope_table", "ssa_linear_workspace_size", "ssa_linear_plan", "ssa_linear",
+            "ssa_rms_norm",
             "ssa_layer_workspace_size", "ssa_layer_forward", "ssa_probe_hbm_read",
             "ssa_probe_hbm_gather", "ssa_probe_mfma_bf16")
 
@@ -575,6 +582,13 @@ def linear_workspace_size(m: int, n: int, k: int) -> int:
     _check(LIB.ssa_linear_workspace_size(int(m), int(n), int(k), ctypes.byref(ws)),
            "ssa_linear_workspace_size")
     return int(ws.value)
+
+
+def linear_plan(m: int, n: int, k: int) -> SsaLinearPlanInfo:
+    """How ssa_linear runs an [m, k] x [n, k]^T product: its tiles and K splits."""
+    info = SsaLinearPlanInfo()
+    _check(LIB.ssa_linear_plan(int(m), int(n), int(k), ctypes.byref(info)), "ssa_linear_plan")
+    return info
 
 
 def linear(x, w, out, epilogue: int = EPILOGUE_NONE, residual=None, workspace=None, stream=None):

@@ -42,6 +42,25 @@ def test_linear_workspace_rule():
     assert b - 256 <= 4 * 6144 * 256 * (4096 // 256)
 
 
+@pytest.mark.parametrize("m,n,k", [(1, 1 << 30, 64), (31, 2 ** 31 - 128, 64), (32, 1 << 30, 64),
+                                   (40, 1 << 30, 64), (64, 1 << 29, 256), (1, 2 ** 31 - 128, 512),
+                                   (2 ** 24, 2048, 64), (2 ** 28, 128, 64), (1500, 1 << 25, 64)])
+def test_linear_plans_the_largest_sizes_as_launches_the_runtime_takes(m, n, k):
+    """A launch holds fewer than 2^32 threads; every size that is taken gets tiles
+    whose grid does."""
+    p = ssa.linear_plan(m, n, k)
+    assert p.tiles_m == -(-m // p.tile_m) and p.tiles_n * p.tile_n == n
+    assert p.tiles_m * p.tiles_n * p.splits * p.threads < 2 ** 32
+
+
+def test_linear_plan_checks_its_arguments():
+    out = ssa.SsaLinearPlanInfo()
+    assert LIB.ssa_linear_plan(4, 100, 64, ctypes.byref(out)) == ssa.SSA_ERR_ARG
+    assert LIB.ssa_linear_plan(4, 128, 64, None) == ssa.SSA_ERR_NULL
+    assert LIB.ssa_linear_plan(0, 128, 64, ctypes.byref(out)) == ssa.SSA_OK
+    assert (out.tile_m, out.tiles_m, out.splits) == (0, 0, 0)
+
+
 def test_rms_norm_rejects_bad_arguments():
     f = ctypes.c_float
     assert LIB.ssa_rms_norm(4, 12, NULL, NULL, f(1e-5), NULL, NULL) == ssa.SSA_ERR_ARG
