@@ -56,8 +56,12 @@ constexpr int kNormThreads = 256;
 constexpr int BK = 64;  // K block: one 128-byte LDS row per operand row
 constexpr int kXcds = 8;
 constexpr float kLog2e = 1.4426950408889634f;
-// From here on 7 rows of 2 K bytes and a chunk pass 32 bits: 64-bit addresses.
+// Rows this long take 64-bit lane addresses: 7 rows of 2 K bytes and a chunk pass
+// 32 bits not far above.
 constexpr int kWideK = 1 << 28;
+// Split tickets at the start of the workspace.
+constexpr size_t kTicketBytes = ssa::kLinearTicketBytes;
+constexpr int kTicketWords = (int)kTicketBytes / 4;
 
 // Reads of the partials: 16-byte buffer loads with the device-coherent cache
 // policy (sc1), the instruction of a device-scope load, so they do not hit a
@@ -295,13 +299,15 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
           wr((mine + (mt * TN + nt) * 256) * 4, __builtin_bit_cast(u32x4, acc[mt][nt]));
     vm_wait<0>();     // this thread's device-scope stores have completed
     __syncthreads();  // everyone's have, and the ring is free
-    // the tile's 4-bit counter: tile % 64 names the word, tile / 64 the nibble
-    uint32_t* const word = a.tickets + tile % 64;
-    const int shift = tile / 64 * 4;
+    // the tile's counter: tile % 64 names the word, tile / 64 the nibble; up to 64
+    // tiles have a whole word each
+    uint32_t* const word = a.tickets + tile % kTicketWords;
+    const int shift = tile / kTicketWords * 4;
+    const uint32_t mask = tiles <= kTicketWords ? ~0u : 15u;
     if (tid == 0) {
       const uint32_t prev =
           __hip_atomic_fetch_add(word, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = (int)((prev >> shift) & 15) == a.splits - 1;
+      s_last = (int)((prev >> shift) & mask) == a.splits - 1;
     }
     __syncthreads();
     if (!s_last) return;
@@ -458,11 +464,12 @@ struct GemmPlan {
 };
 
 constexpr int kCus = 256;
-// Split tickets: a 4-bit counter per tile in the workspace's first 256 bytes,
-// whatever the shape, so that products of different shapes can share a
-// workspace (the partials of one never lie where another's tickets are).
-constexpr size_t kTicketBytes = ssa::kLinearTicketBytes;
-constexpr int kMaxSplitTiles = (int)kTicketBytes * 2, kMaxSplits = 15;
+// Split tickets: a counter per tile in the workspace's first 256 bytes, whatever
+// the shape, so that products of different shapes can share a workspace (the
+// partials of one never lie where another's tickets are): a word each for up to
+// 64 tiles, else 4 bits.
+constexpr int kMaxSplitTiles = kTicketWords * 8;
+constexpr int max_splits(int64_t tiles) { return tiles <= kTicketWords ? 256 : 15; }
 
 // cfg's tiles in (up to) s K splits; one where the tickets do not suffice.
 GemmPlan make_plan(int cfg, int m, int n, int k, int s) {
@@ -472,8 +479,8 @@ GemmPlan make_plan(int cfg, int m, int n, int k, int s) {
   c.tiles_m = (m + cs.bm - 1) / cs.bm;
   c.tiles_n = n / cs.bn;
   c.kblocks = k / BK;
-  s = std::max(1, std::min({s, c.kblocks, kMaxSplits}));
-  if ((int64_t)c.tiles_m * c.tiles_n > kMaxSplitTiles) s = 1;
+  const int64_t tiles = (int64_t)c.tiles_m * c.tiles_n;
+  s = tiles > kMaxSplitTiles ? 1 : std::max(1, std::min({s, c.kblocks, max_splits(tiles)}));
   c.kbps = (c.kblocks + s - 1) / s;
   c.splits = (c.kblocks + c.kbps - 1) / c.kbps;
   c.ws = c.splits > 1 ? kTicketBytes + (size_t)c.tiles_m * c.tiles_n * c.splits * cs.bm * cs.bn * 4 : 0;
@@ -522,22 +529,26 @@ bool launchable(const GemmPlan& c) {
 }
 
 // The cheapest plan by plan_cost over the configurations and 1 .. 12 splits of
-// at least 3 K blocks that leave at most 1100 workgroups.
+// at least 3 K blocks that leave at most 1100 workgroups.  A few tiles on a long K
+// (at least 32 K blocks a split, so K >= 32768) are cut further, up to 256 ways:
+// 1 x 128 x 2^20 91 us, 529 in 12 splits; 16 x 128 x 65536 14 us and 23.
 GemmPlan choose_plan(int m, int n, int k) {
-  if (k >= kWideK) return make_plan(kCfg32x64, m, n, k, 1);
   GemmPlan best{};
   double best_cost = 1e300;
   const bool small_fits = launchable(make_plan(kCfg32x64, m, n, k, 1));
   for (int cfg = 0; cfg < kNumCfgs; ++cfg) {
     const CfgShape& cs = kCfgShapes[cfg];
+    if (k >= kWideK && cfg != kCfg32x64) break;  // the one with 64-bit lane addresses
     // half-empty tiles, and tiles far smaller than a long batch, never win
-    if (n % cs.bn || (small_fits && cs.bm > 32 && cs.bm >= 2 * m) || (cs.bm < 96 && m >= 1024))
+    if (k < kWideK && (n % cs.bn || (small_fits && cs.bm > 32 && cs.bm >= 2 * m) ||
+                       (cs.bm < 96 && m >= 1024)))
       continue;
     // (every size that check_linear takes is launchable in 64 x 128 tiles)
     if (!launchable(make_plan(cfg, m, n, k, 1))) continue;
-    for (int s : {1, 2, 3, 4, 5, 6, 8, 12}) {
+    for (int s : {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
       const GemmPlan c = make_plan(cfg, m, n, k, s);
       if (s > 1 && ((int64_t)c.tiles_m * c.tiles_n * s > 1100 || c.kblocks / s < 3)) break;
+      if (s > 12 && (s > max_splits((int64_t)c.tiles_m * c.tiles_n) || c.kblocks / s < 32)) break;
       const double cost = plan_cost(c, m, n, k);
       if (cost < best_cost) best_cost = cost, best = c;
     }

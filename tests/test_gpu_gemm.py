@@ -166,6 +166,57 @@ def test_linear_tile_edges_match_the_oracle(torch_dev, case):
     assert np.isfinite(to_f32(got)).all()
 
 
+# Few tiles on a long K: more than 15 splits, whose tickets are whole words, with
+# K blocks that do not divide by the splits; the shared workspace's tickets are
+# back at zero (run checks them).
+@pytest.mark.parametrize("m,n,k,epi", [(16, 128, 65536, RES), (33, 512, 40960, NONE),
+                                       (1, 256, 131136, SWIGLU), (64, 512, 131072, NONE)])
+def test_linear_few_tiles_on_a_long_k(torch_dev, m, n, k, epi):
+    from dense_ref import to_f32
+    from paper_2606_05933_amd import ssa
+    p = ssa.linear_plan(m, n, k)
+    say(f"[gpu linear long K] M={m} N={n} K={k} epilogue={epi} splits={p.splits}")
+    assert p.splits > 15 and p.tiles_m * p.tiles_n <= 64
+    x, w_ref, w_dev, res = inputs(m, n, k, epi, seed=900 + m)
+    got, _ = run(torch_dev, m, n, k, epi, x, w_dev, res)
+    ref, tol = reference(x, w_ref, res, epi, np.arange(m))
+    err = np.abs(to_f32(got).astype(np.float64) - ref)
+    say(f"    max_err={err.max():.3e} worst_ratio={(err / tol).max():.3f}")
+    assert np.all(err <= tol)
+
+
+def test_linear_rows_past_32_bit_offsets(torch_dev):
+    """K from 2^28 on takes 64-bit lane addresses.  x is zero but for 3000 places, at
+    both ends of the rows and of the splits' ranges and between, so that the
+    reference needs only those columns of W."""
+    from paper_2606_05933_amd import ssa
+    torch = torch_dev
+    m, n, k = 11, 128, (1 << 28) + 64
+    p = ssa.linear_plan(m, n, k)
+    say(f"[gpu linear wide K] M={m} N={n} K={k} splits={p.splits}")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda")
+    for row in w:
+        row.normal_(generator=g)
+    per = -(-(k // 64) // p.splits) * 64
+    edges = np.concatenate([np.arange(0, k, per), np.arange(per - 1, k, per), [k - 1]])
+    at = np.unique(np.concatenate([np.random.default_rng(5).integers(0, k, 3000 - len(edges)), edges]))
+    at = torch.from_numpy(at).cuda()
+    x = torch.zeros((m, k), dtype=torch.bfloat16, device="cuda")
+    x[:, at] = torch.randn((m, len(at)), generator=g, device="cuda").to(torch.bfloat16)
+    ws = torch.zeros(max(256, ssa.linear_workspace_size(m, n, k)), dtype=torch.uint8, device="cuda")
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ssa.linear(x, w, out, workspace=ws)
+    torch.cuda.synchronize()
+    xs, wt = x[:, at].double(), w[:, at].double().t().contiguous()
+    ref = xs @ wt
+    tol = 2.0 ** -8 * ref.abs() + 2.0 ** -17 * (xs.abs() @ wt.abs())
+    err = (out.double() - ref).abs()
+    say(f"    max_err={err.max().item():.3e} worst_ratio={(err / tol).max().item():.3f}")
+    assert bool((err <= tol).all())
+    assert int(ws[:256].count_nonzero()) == 0
+
+
 def test_linear_products_of_different_shapes_share_a_workspace(torch_dev):
     """Calls ordered on one stream may share a workspace whatever their shapes: a
     product's partial tiles must not lie where another's tickets are.  Each round
