@@ -26,12 +26,15 @@
 //  * Rows of x past M are read from the 8-row piece of row M - 1 (in bounds) and
 //    never stored.
 //  * With one M tile, W is read once by the whole chip: its copies carry the
-//    non-temporal hint where that pays (kStreamMaxM), and tile t starts its K loop
-//    at block 3 t so that neighbouring tiles, whose rows are a power of two apart,
-//    do not all walk the same memory channels (24 x 28672 x 4096 with W out of the
-//    caches: 57 -> 37 us, 6.3 TB/s; the hint alone, with all tiles at block 0: 39).
-//    With several M tiles neither: they share W and x panels through the caches,
-//    which wants them on the same K block.
+//    non-temporal hint, and tile t starts its K loop at block 3 t so that
+//    neighbouring tiles, whose rows are a power of two apart, do not all walk the
+//    same memory channels.  24 x 28672 x 4096 with W out of the caches, as a
+//    model's weights are: 37.1 us (6.3 TB/s); without the stagger 39.2, without the
+//    hint 42.2, with neither 44.6.  A call repeated on weights that the last-level
+//    cache could hold loses by the hint (128 x 28672 x 4096: 47.5 us, 37.5
+//    without); a decoder layer of 128 decodes takes 272 us with it and 280 without
+//    it past 32 rows.  With several M tiles neither: they share W and x panels
+//    through the caches, which wants them on the same K block.
 //  * Too few tiles to fill the chip: K is split; each split writes its fp32
 //    tile with device-scope stores, takes a ticket, and the last one adds the
 //    splits in split order (the result does not depend on arrival order),
@@ -95,7 +98,6 @@ struct GemmArgs {
   float* part;
   int m, n, k;
   int tiles_m, tiles_n, splits, kbps, kblocks, group;
-  int stagger;  // K blocks by which a tile starts behind the one before it
 };
 
 // A tile configuration: NWM x NWN waves, each owning TM x TN MFMA tiles of
@@ -138,9 +140,10 @@ __device__ __forceinline__ void block_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// MODE: kPlain; kStream, W copies with the non-temporal hint; kWide, rows too long
-// for a 32-bit lane offset (7 rows of 2 K bytes): 64-bit lane addresses.
-enum { kPlain, kStream, kWide };
+// MODE: kShared, several M tiles; kStream, one M tile (W copies with the
+// non-temporal hint, staggered K loops); kWide, rows too long for a 32-bit lane
+// offset (7 rows of 2 K bytes): 64-bit lane addresses.
+enum { kShared, kStream, kWide };
 template <class C, int EPI, int MODE>
 __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a) {
   constexpr int TM = C::TM, TN = C::TN, STAGES = C::STAGES, LOADS = C::kLoads;
@@ -162,7 +165,7 @@ __global__ __launch_bounds__(C::kThreads, C::OCC) void linear_kernel(GemmArgs a)
   const int m0 = tm * BM, n0 = tn * BN;
   const int kb0 = split * a.kbps;
   const int nkb = min(a.kbps, a.kblocks - kb0);
-  const int rot = (tile * a.stagger) % nkb;  // the K block this tile starts with
+  const int rot = MODE == kStream ? (tile * 3) % nkb : 0;  // the K block this tile starts with
 
   // Copy r of this wave fills 1 KB piece p = kWaves r + w of a stage: pieces
   // below BM / 8 hold x rows 8p..8p+7, the rest W rows; lane i fetches the
@@ -465,14 +468,6 @@ struct GemmPlan {
 };
 
 constexpr int kCus = 256;
-// W copies carry the non-temporal hint up to this many rows, or where W is larger
-// than the last-level cache.  us with it / without, W out of the caches: 24 x 28672
-// x 4096 37.1 / 42.2, 1 x 8192 x 8192 23.3 / 25.0, 128 x 57344 x 8192 178 / 190; but
-// 64 x 28672 x 4096 39.9 / 41.4, 128 x 28672 x 4096 48.2 / 49.5 and 128 x 8192 x
-// 8192 37.9 / 36.2, where a W that is still cached (a repeated call) runs at 38.9 /
-// 35.2, 47.5 / 37.5 and 36.6 / 29.3.
-constexpr int kStreamMaxM = 32;
-constexpr int64_t kLastLevelBytes = INT64_C(256) << 20;
 // Split tickets: a counter per tile in the workspace's first 256 bytes, whatever
 // the shape, so that products of different shapes can share a workspace (the
 // partials of one never lie where another's tickets are): a word each for up to
@@ -586,10 +581,8 @@ void launch_mode(const GemmPlan& c, int epilogue, const GemmArgs& a, hipStream_t
 
 template <class C>
 void launch_cfg(const GemmPlan& c, int epilogue, const GemmArgs& a, hipStream_t s) {
-  if (c.tiles_m == 1 && (a.m <= kStreamMaxM || (int64_t)a.n * a.k * 2 > kLastLevelBytes))
-    launch_mode<C, kStream>(c, epilogue, a, s);
-  else
-    launch_mode<C, kPlain>(c, epilogue, a, s);
+  if (c.tiles_m == 1) launch_mode<C, kStream>(c, epilogue, a, s);
+  else launch_mode<C, kShared>(c, epilogue, a, s);
 }
 
 // Launch a planned product; the workspace has been checked against c.ws.
@@ -601,8 +594,7 @@ int launch_linear(const GemmPlan& c, int m, int n, int k, int epilogue, const ui
              c.ws > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + kTicketBytes) : nullptr,
              m, n, k, c.tiles_m, c.tiles_n, c.splits, c.kbps, c.kblocks,
              // up to 8 M tiles: all of them beside each N tile; more: groups of 4
-             c.tiles_m <= 8 ? c.tiles_m : 4,
-             c.tiles_m == 1 ? 3 : 0};
+             c.tiles_m <= 8 ? c.tiles_m : 4};
   (void)hipGetLastError();
   switch (c.cfg) {
     case kCfg32x64:
