@@ -57,6 +57,7 @@ struct RopeArgs {
   const int32_t* bt;
   int hq, hkv, maxp;
   int grouped_segs;  // segments run by head groups; the others are single rows
+  int workgroups;
 };
 
 // Heads per workgroup of a grouped segment: group y < rot_groups rotates
@@ -64,6 +65,9 @@ struct RopeArgs {
 // value heads.
 constexpr int kHeadGroup = 8;
 constexpr int kSingleMaxHeads = 16 * kHeadGroup;  // rotated heads of one row per workgroup
+// Workgroups go in rows of this many: one row of more than 2^24 workgroups would
+// pass the 2^32 threads of a grid's x dimension (millions of short chunks).
+constexpr int kGridRow = 1 << 16;
 
 // Latency bounds it at small T: launch, the segment's record (in host memory
 // where the plan is), the rows, the stores.  A decode row has 1/16 of a chunk
@@ -84,7 +88,9 @@ __global__ __launch_bounds__(kLayerThreads) void rope_append_kernel(RopeArgs a) 
   const PlanHeader* hdr = reinterpret_cast<const PlanHeader*>(a.plan);
   // workgroups of the grouped segments (segment-major), then one per single row
   const int nrot = a.hq + a.hkv, rot_groups = (nrot + HG - 1) / HG;
-  const int groups = rot_groups + (a.hkv + HG - 1) / HG, wg = (int)blockIdx.x;
+  const int groups = rot_groups + (a.hkv + HG - 1) / HG;
+  const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (wg >= a.workgroups) return;
   const bool single = wg >= a.grouped_segs * groups;
   const int seg = single ? a.grouped_segs + (wg - a.grouped_segs * groups) : wg / groups;
   const int group = single ? 0 : wg % groups;
@@ -231,11 +237,14 @@ int ssa_rope_append(const ssa_shape* shape, const void* plan_host, const void* p
   // heads); the plan lists the segments of chunk requests first.
   const int32_t grouped =
       h->hq + h->hkv <= kSingleMaxHeads ? h->num_chunk_segments : h->num_segments;
-  RopeArgs a{static_cast<const uint8_t*>(plan_dev), h->hash, h->off_segments, qkv, cos_sin,
-             q_out, k_cache, v_cache, block_table, h->hq, h->hkv, h->max_pages_per_req, grouped};
   const int32_t groups = (h->hq + h->hkv + kHeadGroup - 1) / kHeadGroup +
                          (h->hkv + kHeadGroup - 1) / kHeadGroup;
-  const dim3 grid(grouped * groups + (h->num_segments - grouped));
+  const int64_t wgs = (int64_t)grouped * groups + (h->num_segments - grouped);
+  if (wgs > INT32_MAX) return SSA_ERR_ARG;
+  RopeArgs a{static_cast<const uint8_t*>(plan_dev), h->hash, h->off_segments, qkv, cos_sin,
+             q_out, k_cache, v_cache, block_table, h->hq, h->hkv, h->max_pages_per_req, grouped,
+             (int32_t)wgs};
+  const dim3 grid(wgs < kGridRow ? wgs : kGridRow, (wgs + kGridRow - 1) / kGridRow);
   if (h->head_dim == 128)
     hipLaunchKernelGGL(rope_append_kernel<128>, grid, dim3(kLayerThreads), 0,
                        static_cast<hipStream_t>(stream), a);

@@ -104,6 +104,39 @@ def test_rope_append_single_rows(torch_dev, hq, hkv, d, cu):
     run_case(torch_dev, hq, hkv, d, cu, seed=hq + d)
 
 
+@pytest.mark.parametrize("c", [1, 2])
+def test_rope_append_of_more_workgroups_than_a_grid_row(torch_dev, c):
+    """70000 requests of one row, or of two (by head groups), run in more than one
+    row of the grid: the same bits as in calls of at most 20000 requests."""
+    from paper_2606_05933_amd import ssa
+    torch = torch_dev
+    n, d, hq, hkv = 70000, 64, 1, 1
+    say(f"[gpu rope grid rows] requests={n} rows each={c}")
+    g = torch.Generator(device="cuda").manual_seed(c)
+    qkv = torch.randn((n * c, 3 * d), generator=g, device="cuda").to(torch.bfloat16)
+    u = np.random.default_rng(c).integers(0, 14, n).astype(np.int32)
+    cos_sin = torch.from_numpy(ssa.rope_cos_sin(16, d)).cuda()
+
+    def call(at, m):
+        shape = ssa.make_shape(hq, hkv, d, m, 1, 0.125)
+        plan, _ = ssa.ssa_plan(shape, np.full(m, c, np.int32), u[at:at + m])
+        plan = torch.from_numpy(np.asarray(plan).copy())
+        q = torch.zeros((m * c, hq, d), dtype=torch.bfloat16, device="cuda")
+        k = torch.zeros((m, hkv, 16, d), dtype=torch.bfloat16, device="cuda")
+        v = torch.zeros((m, hkv, d, 16), dtype=torch.bfloat16, device="cuda")
+        table = torch.arange(m, dtype=torch.int32, device="cuda").view(m, 1)
+        ssa.rope_append(shape, plan, plan.cuda(), qkv[at * c:(at + m) * c], cos_sin, q, k, v, table)
+        torch.cuda.synchronize()
+        return q, k, v
+
+    whole = call(0, n)
+    parts = [call(at, min(20000, n - at)) for at in range(0, n, 20000)]
+    for i in range(3):
+        assert torch.equal(whole[i].view(torch.int16),
+                           torch.cat([p[i] for p in parts]).view(torch.int16))
+        assert int((whole[i] != 0).any(dim=-1).sum()) >= n
+
+
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_rope_append_then_attention(torch_dev, case):
     from dense_ref import to_bf16
