@@ -826,6 +826,13 @@ int build(const ssa_shape* s, const int32_t* q_len, const int32_t* ctx_len, int3
     hv = fnv1a(hv, q_len, sizeof(int32_t) * n);
     hv = fnv1a(hv, ctx_len, sizeof(int32_t) * n);
   }
+  // How chunk tiles are cut by themselves is this planner's own: a plan kept from
+  // another version of it must not pass for this one, whose item count the launch
+  // takes from the host's copy.
+  if (in.num_chunk_items > 0 && tu.chunk_split_keys == 0) {
+    const int64_t cut[3] = {in.num_chunk_items, in.num_merge_groups, h.ws_bytes};
+    hv = fnv1a(hv, cut, sizeof cut);
+  }
   h.hash = hv;
   return SSA_OK;
 }

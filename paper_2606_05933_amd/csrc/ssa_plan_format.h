@@ -41,7 +41,7 @@ enum ItemKind : int32_t { kItemChunk = 0, kItemDecode = 1 };
 struct PlanHeader {
   uint32_t magic;
   uint32_t version;
-  uint64_t hash;  // FNV-1a of the shape, the tuning and the length arrays
+  uint64_t hash;  // FNV-1a of the shape, the tuning, the length arrays and the chunk cut
   int32_t num_reqs, num_tokens;
   int32_t num_items, num_chunk_items, num_decode_items, num_groups, num_segments;
   int32_t hq, hkv, head_dim, page_size, max_pages_per_req, num_pages;

@@ -317,6 +317,18 @@ def test_chunk_pieces_fit_the_scratch(hq, hkv, q, ctx):
     assert ssa.ssa_plan_size(shape, q, ctx)[1] <= 32 << 20
 
 
+def test_plans_of_another_cut_do_not_share_a_hash():
+    """A launch takes the item count from the host's copy of the plan and the items
+    from the device's, and the hash is what holds them together.  An earlier
+    planner cut this batch into 176 items under the hash below: kept on the device,
+    its plan must not pass for the present one's 256 items.  Where a plan cannot
+    differ (no chunk rows), it has not changed either."""
+    blob, info = ssa.ssa_plan(ssa.make_shape(32, 8, 128, 300, 256, 0.125), [250], [3001])
+    assert info.num_items != 176 and parse(blob)[0]["hash"] != 0x5C6E00B4DA51E9C4
+    blob, _ = ssa.ssa_plan(ssa.make_shape(32, 8, 128, 300, 256, 0.125), [1], [3001])
+    assert parse(blob)[0]["hash"] == 0x4B43C7A01CAC6FC3
+
+
 def test_plan_is_deterministic():
     q_len = np.array([300, 1, 1, 1], np.int32)
     ctx_len = np.array([0, 5, 900, 40], np.int32)
