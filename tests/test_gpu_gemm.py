@@ -35,18 +35,18 @@ NONE, RES, SWIGLU = 0, 1, 2
 CASES = [  # (M, N, K, epilogue)
     (1, 128, 64, NONE),
     (37, 256, 320, NONE),
-    (130, 384, 4096, NONE),        # 6 tiles: K split 16 ways
+    (130, 384, 4096, NONE),        # 30 tiles of 32 x 64, K split
     (300, 640, 1024, RES),
     (129, 256, 2048, SWIGLU),
     (28, 6144, 4096, NONE),        # a decode-only batch through the QKV projection
-    (520, 4096, 14336, RES),       # the down projection of a mixed batch, K split 3
+    (520, 4096, 14336, RES),       # the down projection of a mixed batch, K split
     (1000, 1024, 512, SWIGLU),
     (257, 28672, 4096, SWIGLU),    # gate/up projection
-    # tiles that overfill the chip by part of a round
-    (700, 11264, 512, RES),        # 528 tiles of 128 x 128, ragged M
-    (1100, 8192, 256, NONE),       # 576 tiles, 4 K blocks each
-    (640, 28672, 4096, SWIGLU),    # 1120 tiles of 128 x 128
-    (1152, 28672, 4096, SWIGLU),   # 560 tiles of 256 x 256
+    # more tiles than one round of the chip holds, or a part of a round
+    (700, 11264, 512, RES),        # ragged M
+    (1100, 8192, 256, NONE),       # 4 K blocks
+    (640, 28672, 4096, SWIGLU),
+    (1152, 28672, 4096, SWIGLU),
     # where 192-row tiles fit one round of the chip and 128- or 160-row ones do not
     (370, 28672, 1024, SWIGLU),    # ragged M
     (384, 28672, 4096, NONE),
@@ -130,10 +130,11 @@ def test_linear_matches_the_oracle(torch_dev, case):
     assert np.all(err <= tol)
 
 
-# Every tile configuration with one and several M tiles, unsplit and K-split, at
-# ragged M (the last rows of a tile, of a 16-row tile and of an 8-row copy piece
-# cut), one K block (fewer than the ring's stages), and K blocks that do not
-# divide by the splits.
+# The tile configurations with one and several M tiles, unsplit and K-split (what a
+# size runs as, and that the list leaves none of them out, is checked without a
+# GPU in test_layer_boundary.py), at ragged M (the last rows of a tile, of a
+# 16-row tile and of an 8-row copy piece cut), one K block (fewer than the ring's
+# stages), and K blocks that do not divide by the splits.
 TILE_EDGES = [
     (1, 128, 64, NONE), (1, 128, 2112, RES), (33, 128, 64, SWIGLU), (33, 128, 2112, NONE),   # 32 x 64
     (7, 384, 640, SWIGLU), (9, 384, 3200, NONE), (31, 1280, 448, RES),
@@ -148,6 +149,18 @@ TILE_EDGES = [
     (1137, 6784, 64, NONE), (1137, 6784, 192, RES),                                           # 192 x 128, two per CU
     (775, 6656, 64, SWIGLU), (775, 6656, 448, NONE),                                          # 256 x 128
     (1539, 7424, 64, NONE), (1539, 7424, 128, RES), (1539, 7424, 576, SWIGLU),                # 256 x 256
+    # one M tile, unsplit
+    (33, 8576, 64, NONE), (65, 8576, 64, RES), (97, 8320, 64, SWIGLU), (138, 28672, 64, NONE),
+    (196, 28672, 64, SWIGLU), (132, 57344, 64, RES), (161, 57344, 64, NONE), (193, 57344, 64, RES),
+    # one M tile, K-split
+    (33, 8320, 7168, RES), (67, 8320, 4096, SWIGLU), (110, 8320, 3200, NONE),
+    (134, 11008, 7232, RES), (130, 5504, 7232, SWIGLU), (193, 5504, 10240, NONE),
+    (169, 11008, 14336, RES), (193, 28672, 14336, NONE),
+    # several M tiles, K-split
+    (302, 2176, 5120, SWIGLU), (2076, 256, 10240, NONE), (2038, 256, 5120, RES),
+    (2067, 512, 7168, SWIGLU), (2059, 1024, 10240, NONE), (1297, 3072, 7168, RES),
+    (2401, 896, 10240, SWIGLU), (1771, 2816, 14336, RES),
+    (783, 8448, 8192, NONE),                                  # more than 256 tiles split
 ]
 
 

@@ -53,6 +53,25 @@ def test_linear_plans_the_largest_sizes_as_launches_the_runtime_takes(m, n, k):
     assert p.tiles_m * p.tiles_n * p.splits * p.threads < 2 ** 32
 
 
+def test_gpu_cases_cover_the_linear_tile_configurations():
+    """Every tile configuration, with one and with several M tiles, unsplit and
+    K-split, is in the sizes that test_gpu_gemm.py compares with the oracle: a change
+    of the rule that picks them must not drop one."""
+    from test_gpu_gemm import CASES, TILE_EDGES
+    tiles = [(32, 64, 256), (64, 64, 256), (64, 128, 256), (96, 64, 256), (96, 128, 256),
+             (128, 64, 256), (128, 128, 512), (160, 128, 256), (192, 128, 256), (192, 128, 512),
+             (256, 128, 512), (256, 256, 512)]
+    want = {t + (many, split) for t in tiles for many in (False, True) for split in (False, True)}
+    have, split_tiles = set(), 0
+    for m, n, k, _ in CASES + TILE_EDGES:
+        p = ssa.linear_plan(m, n, k)
+        have.add((p.tile_m, p.tile_n, p.threads, p.tiles_m > 1, p.splits > 1))
+        if p.splits > 1:
+            split_tiles = max(split_tiles, p.tiles_m * p.tiles_n)
+    assert want <= have, sorted(want - have)
+    assert split_tiles > 256  # the upper split tickets of a word
+
+
 def test_linear_plan_checks_its_arguments():
     out = ssa.SsaLinearPlanInfo()
     assert LIB.ssa_linear_plan(4, 100, 64, ctypes.byref(out)) == ssa.SSA_ERR_ARG
