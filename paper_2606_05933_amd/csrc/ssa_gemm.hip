@@ -22,7 +22,8 @@
 //    landed and this block's reads are done, so its stage is refilled at once),
 //    and the copies go out one by one between the rows of MFMAs.  Reading a
 //    block's fragments only after its barrier left the matrix cores idle for
-//    the LDS reads of every block (4096 x 4096 x 14336: 410 us, now 337 us).
+//    the LDS reads of every block (4096 x 4096 x 14336 with the residual: 397 us,
+//    360 with this loop and the tiles chosen by plan_cost).
 //  * Rows of x past M are read from the 8-row piece of row M - 1 (in bounds) and
 //    never stored.
 //  * With one M tile, W is read once by the whole chip: its copies carry the
@@ -495,9 +496,10 @@ GemmPlan make_plan(int cfg, int m, int n, int k, int s) {
 // one and (OCC 2) two of them on every CU.  Fitted, with the constants of
 // plan_cost, to 290 products timed on MI355X in every configuration and 1 to 12
 // splits, weights out of the caches (M = 1 .. 4096; N x K of the Llama-3-8B
-// projections and 640 x 640 .. 16384 x 8192): the plan picked is 1.2% slower than
-// the fastest measured on the mean (14% at worst) and takes 0.68 of hipBLASLt's
-// time on the geometric mean (0.94 at M = 2176, 1.1 at M = 4096).
+// projections and 640 x 640 .. 16384 x 8192).  On 286 other products (M = 4 .. 1400,
+// 2048 x 2048 .. 57344 x 8192) the plan picked takes 1.01 of the time of the fastest
+// plan on the mean and 1.23 at worst; on the Llama-3-8B projections 0.69 of
+// hipBLASLt's time for M <= 256, 0.98 from 384 to 1152 and 1.12 from 2176 on.
 constexpr double kBlockUs[kNumCfgs][2] = {
     {0.182, 0.293}, {0.239, 0.475}, {0.380, 0.629}, {0.281, 0.281}, {0.453, 0.453}, {0.379, 0.379},
     {0.521, 0.521}, {0.832, 1.126}, {0.662, 0.662}, {0.924, 1.278}, {0.827, 0.827}, {1.447, 1.447}};

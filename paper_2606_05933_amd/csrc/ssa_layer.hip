@@ -2,7 +2,8 @@
 //
 // ssa_rope_append: for each append segment of the plan (consecutive new
 // tokens of one request inside one page, at most 16), workgroups of 8 heads
-// each; for a decode request's single row, one workgroup for all its heads.  A rotating workgroup rotates 8 of the segment's query and key heads
+// each; for a decode request's single row, one workgroup for all its heads.  A
+// rotating workgroup rotates 8 of the segment's query and key heads
 // (rotate-half pairs (i, i + D/2), cos/sin from the position's row of the
 // table) and writes the queries to q_out and the keys to their slots of the
 // key page (slot-major rows); a value workgroup stages 8 value heads' rows in
