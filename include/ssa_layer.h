@@ -74,7 +74,9 @@ enum {
  *        chip).  Its first 256 bytes are split tickets, whatever the sizes: zero
  *        before the first call (a zeroed allocation), and zero again after every
  *        call.  Calls that share a workspace, of one size or several, must be
- *        ordered on one stream.
+ *        ordered on one stream.  With less, products of at least 128 tiles of 64
+ *        tokens by 128 outputs (M <= 64: of 64 tiles) run in one pass over K,
+ *        somewhat slower; smaller ones return SSA_ERR_WORKSPACE.
  * Requires N % 128 == 0 and K % 64 == 0; M >= 0 (M == 0 does nothing); M K and N K
  * below 2^40 and (M / 32 + 1) (N / 128) at most 2^24.
  * Results do not depend on the launch order of workgroups: split partials are

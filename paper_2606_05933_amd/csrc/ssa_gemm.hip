@@ -546,7 +546,7 @@ bool launchable(const GemmPlan& c) {
 // at least 3 K blocks that leave at most 1100 workgroups.  A few tiles on a long K
 // (at least 32 K blocks a split, so K >= 32768) are cut further, up to 256 ways:
 // 1 x 128 x 2^20 91 us, 529 in 12 splits; 16 x 128 x 65536 14 us and 23.
-GemmPlan choose_plan(int m, int n, int k) {
+GemmPlan choose_plan(int m, int n, int k, int most_splits = 256) {
   GemmPlan best{};
   double best_cost = 1e300;
   const bool small_fits = launchable(make_plan(kCfg32x64, m, n, k, 1));
@@ -560,6 +560,7 @@ GemmPlan choose_plan(int m, int n, int k) {
     // (every size that check_linear takes is launchable in 64 x 128 tiles)
     if (!launchable(make_plan(cfg, m, n, k, 1))) continue;
     for (int s : {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
+      if (s > most_splits) break;
       const GemmPlan c = make_plan(cfg, m, n, k, s);
       if (s > 1 && ((int64_t)c.tiles_m * c.tiles_n * s > 1100 || c.kblocks / s < 3)) break;
       if (s > 12 && (s > max_splits((int64_t)c.tiles_m * c.tiles_n) || c.kblocks / s < 32)) break;
@@ -568,6 +569,15 @@ GemmPlan choose_plan(int m, int n, int k) {
     }
   }
   return best;
+}
+
+// Products that run without a workspace too, in one pass over K: those whose tiles
+// of 64 x 128 give half of the CUs one (a quarter of them up to 64 tokens, where
+// the weights' bytes bound it).  The splits they have with a workspace gain up to a
+// fifth, or nothing: 39 x 10240 x 6528 26.6 us, 32.3 without; 1600 x 4096 x 14336
+// 168 and 175; 391 x 8832 x 7872 72 and 72.
+bool runs_unsplit(int m, int n) {
+  return (int64_t)((m + 63) / 64) * (n / 128) >= (m <= 64 ? kCus / 4 : kCus / 2);
 }
 
 template <class C, int MODE>
@@ -676,8 +686,11 @@ int ssa_linear(int32_t m, int32_t n, int32_t k, int32_t epilogue, const uint16_t
   if (rc) return rc;
   if (m == 0) return SSA_OK;
   if (!x || !w || !out || (epilogue == SSA_EPILOGUE_RESIDUAL && !residual)) return SSA_ERR_NULL;
-  const GemmPlan c = choose_plan(m, n, k);
-  if (c.ws > 0 && (!workspace || ws_bytes < c.ws)) return SSA_ERR_WORKSPACE;
+  GemmPlan c = choose_plan(m, n, k);
+  if (c.ws > 0 && (!workspace || ws_bytes < c.ws)) {
+    if (!runs_unsplit(m, n)) return SSA_ERR_WORKSPACE;
+    c = choose_plan(m, n, k, 1);
+  }
   return launch_linear(c, m, n, k, epilogue, x, w, residual, out, workspace,
                        static_cast<hipStream_t>(stream));
 }

@@ -179,6 +179,30 @@ def test_linear_tile_edges_match_the_oracle(torch_dev, case):
     assert np.isfinite(to_f32(got)).all()
 
 
+@pytest.mark.parametrize("m,n,k,epi", [(39, 10240, 6528, RES), (189, 8576, 6720, NONE),
+                                       (391, 8832, 7872, SWIGLU), (1600, 4096, 14336, RES)])
+def test_linear_without_a_workspace(torch_dev, m, n, k, epi):
+    """Sizes with enough tiles run without a workspace, though they are split with
+    one."""
+    from dense_ref import to_f32
+    from paper_2606_05933_amd import ssa
+    torch = torch_dev
+    say(f"[gpu linear without workspace] M={m} N={n} K={k} epilogue={epi}")
+    assert ssa.linear_plan(m, n, k).splits > 1
+    x, w_ref, w_dev, res = inputs(m, n, k, epi, seed=950 + m)
+    out = torch.full((m, n // 2 if epi == SWIGLU else n), float("nan"), dtype=torch.bfloat16,
+                     device="cuda")
+    ssa.linear(dev_bf16(torch, x), dev_bf16(torch, w_dev), out, epi,
+               residual=None if res is None else dev_bf16(torch, res))
+    torch.cuda.synchronize()
+    got = out.view(torch.int16).cpu().numpy().view(np.uint16)
+    rows = np.unique(np.r_[0, np.arange(max(0, m - 40), m), np.arange(0, m, 61)])
+    ref, tol = reference(x, w_ref, res, epi, rows)
+    err = np.abs(to_f32(got[rows]).astype(np.float64) - ref)
+    say(f"    max_err={err.max():.3e} worst_ratio={(err / tol).max():.3f}")
+    assert np.all(err <= tol) and np.isfinite(to_f32(got)).all()
+
+
 # Few tiles on a long K: more than 15 splits, whose tickets are whole words, with
 # K blocks that do not divide by the splits; the shared workspace's tickets are
 # back at zero (run checks them).

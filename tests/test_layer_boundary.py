@@ -80,6 +80,16 @@ def test_linear_plan_checks_its_arguments():
     assert (out.tile_m, out.tiles_m, out.splits) == (0, 0, 0)
 
 
+@pytest.mark.parametrize("m,n,k", [(28, 6144, 4096), (1, 128, 8192), (128, 4096, 14336)])
+def test_linear_refuses_a_small_product_without_its_workspace(m, n, k):
+    rc, need = ws(m, n, k)
+    assert rc == 0 and need > 0
+    fake = ctypes.c_void_p(1 << 40)
+    for buf, nbytes in ((NULL, need), (fake, need - 1), (fake, 0)):
+        assert LIB.ssa_linear(m, n, k, 0, fake, fake, NULL, fake, buf, ctypes.c_size_t(nbytes),
+                              NULL) == ssa.SSA_ERR_WORKSPACE
+
+
 def test_rms_norm_rejects_bad_arguments():
     f = ctypes.c_float
     assert LIB.ssa_rms_norm(4, 12, NULL, NULL, f(1e-5), NULL, NULL) == ssa.SSA_ERR_ARG
